@@ -420,7 +420,7 @@ sop_status sop_propagate_trapezoid_noalloc(sop_plan* plan, void* psi, int count,
  * to 65535 points).  psi_src and psi_dst are device buffers and must differ.
  * Runs asynchronously on dst's stream (psi_src must be ready there); the
  * axis matrices and intermediate states live in a workspace that dst keeps
- * and grows on demand (16 bytes per matrix entry and per intermediate
+ * and grows on demand (8 bytes per matrix entry, 16 per intermediate
  * element; growing it synchronises dst's stream), released with dst.  The
  * matrices are formed on the first call and again only when the source
  * grid (lengths and box) differs from the previous call's. */

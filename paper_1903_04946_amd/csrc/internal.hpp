@@ -255,22 +255,43 @@ size_t trap_scratch_bytes();
 hipError_t trap_scratch(hipStream_t stream, void** out);
 
 // kernels_interp.hip: trigonometric interpolation between uniform grids.
-// Complex FP64 product C[b] = A[b] B[b] (M x K by K x N) with element and
-// batch strides; A needs sak = 1 or sai = 1, B sbj = 1 or sbk = 1.
-struct CgemmArgs {
-  const double2* A = nullptr;
-  const double2* B = nullptr;
-  double2* C = nullptr;
-  int M = 0, N = 0, K = 0;
-  long long sai = 0, sak = 0, sbk = 0, sbj = 0, sci = 0, scj = 0;
-  long long bsa = 0, bsb = 0, bsc = 0;
+// Interval [j0, j0 + nj) of the nd destination points that lie in the source
+// box (nj = 0: none); the rest take zero.
+void interp_inside(int n, double lo, double hi, int nd, double lod, double hid, int* j0, int* nj);
+// Wt [n][ldw]: the real interpolation matrix, transposed, for the destination
+// points of that interval (columns nj..ldw-1 zero; ldw a multiple of 128).
+hipError_t interp_weights(hipStream_t s, double* Wt, int n, double lo, double hi, int nd,
+                          double lod, double hid, int j0, int nj, int ldw);
+// Zeros outside the box of intervals [j0, j0 + nj) of S states on an
+// n[0] x n[1] x n[2] grid.
+struct InterpZero {
+  double2* out = nullptr;
+  int n[3] = {1, 1, 1}, j0[3] = {0, 0, 0}, nj[3] = {1, 1, 1};
+  int S = 1;
 };
-// W [nd][n]: the interpolation matrix from the n-point grid on [lo, hi) to the
-// nd-point grid on [lod, hid).
-hipError_t interp_weights(hipStream_t s, double2* W, int n, double lo, double hi, int nd,
-                          double lod, double hid);
-hipError_t cgemm(hipStream_t s, const CgemmArgs& g, int batch);
-
+hipError_t interp_zero(hipStream_t s, const InterpZero& g);
+// One axis of the interpolation: C(j, col) = sum_m Wt[m][j] X(m, col) for
+// M points j, K samples m and N complex columns, `batch` times.
+// Not krow: X[b][m * ldx + col], C[b][j * ldc + (col / cdiv) * crow + col % cdiv].
+// krow (the contiguous axis): X[b][col * K + m], C[b][col * ldc + j].
+// Strides in complex elements.
+struct InterpAxis {
+  const double* Wt = nullptr;
+  int ldw = 0;
+  const double2* X = nullptr;
+  double2* C = nullptr;
+  int M = 0, K = 0, N = 0, batch = 1;
+  long long ldx = 0, bsx = 0, ldc = 0, bsc = 0;
+  long long crow = 0;
+  int cdiv = 1;
+  // set by the launcher: row tiles, column panels, elements of one X[b]
+  int nm = 0, npan = 0;
+  uint32_t xel = 0;
+};
+hipError_t interp_axis(hipStream_t s, const InterpAxis& g, bool krow);
+// 1D grids: out[s * nd + j] = sum_m Wt[m][j] X[s * n + m], j < nj.
+hipError_t interp_rows(hipStream_t s, const double* Wt, int ldw, int n, int S, int nj,
+                       const double2* X, double2* out, int nd);
 // kernels_aux.hip
 // tile = 0: [u][entry][point] (1D); tile = C: the z-pass tile layout (3D).
 hipError_t form_vexp(const DevView& d, const double* vraw_dev, const double* taus, int ntau,

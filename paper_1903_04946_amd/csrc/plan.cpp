@@ -1083,15 +1083,42 @@ sop_status sop_interpolate(const sop_plan* src, const void* psi_src, sop_plan* d
   for (int a = 0; a < nax; ++a)
     if (dst->n[a] > 65535) return fail(SOP_ERR_UNSUPPORTED, "destination axis too long");
   const int S = src->S;
-  // axis a of the arrays: 0 slowest; 1D grids use axis 0 only
-  const long long ns[3] = {src->n[0], nax == 3 ? src->n[1] : 1, nax == 3 ? src->n[2] : 1};
-  const long long nd[3] = {dst->n[0], nax == 3 ? dst->n[1] : 1, nax == 3 ? dst->n[2] : 1};
-  // workspace: the axis matrices, then (3D) the state after z and after y
-  size_t wel = 0;
-  for (int a = 0; a < nax; ++a) wel += (size_t)nd[a] * ns[a];
-  const size_t t1 = nax == 3 ? (size_t)S * ns[0] * ns[1] * nd[2] : 0;
-  const size_t t2 = nax == 3 ? (size_t)S * ns[0] * nd[1] * nd[2] : 0;
-  const size_t need = (wel + t1 + t2) * sizeof(double2);
+  // axis a of the arrays: 0 slowest; 1D grids use axis 2, the contiguous one
+  const int a0 = nax == 3 ? 0 : 2;
+  long long ns[3] = {1, 1, 1}, nd[3] = {1, 1, 1};
+  int j0[3] = {0, 0, 0}, nj[3] = {1, 1, 1};
+  size_t ldw[3] = {0, 0, 0};
+  for (int a = a0; a < 3; ++a) {
+    const int i = a - a0;
+    ns[a] = src->n[i];
+    nd[a] = dst->n[i];
+    sop::interp_inside(src->n[i], src->lo[i], src->hi[i], dst->n[i], dst->lo[i], dst->hi[i],
+                       &j0[a], &nj[a]);
+    ldw[a] = ((size_t)nj[a] + 127) / 128 * 128;  // whole row tiles
+  }
+  const bool empty = nj[0] == 0 || nj[1] == 0 || nj[2] == 0;
+  // workspace: the axis matrices (an axis whose grids equal an earlier axis'
+  // shares its matrix), then (3D) the state after z and after y, both over
+  // the destination points inside the source box only
+  int share[3] = {0, 1, 2};
+  size_t woff[3] = {0, 0, 0}, wel = 0;
+  for (int a = a0; a < 3; ++a) {
+    for (int b = a0; b < a && share[a] == a; ++b) {
+      const int i = a - a0, k = b - a0;
+      if (src->n[i] == src->n[k] && src->lo[i] == src->lo[k] && src->hi[i] == src->hi[k] &&
+          dst->n[i] == dst->n[k] && dst->lo[i] == dst->lo[k] && dst->hi[i] == dst->hi[k])
+        share[a] = b;
+    }
+    if (share[a] != a) {
+      woff[a] = woff[share[a]];
+      continue;
+    }
+    woff[a] = wel;
+    wel += (size_t)ns[a] * ldw[a];
+  }
+  const size_t t1 = nax == 3 ? (size_t)S * ns[0] * ns[1] * nj[2] : 0;
+  const size_t t2 = nax == 3 ? (size_t)S * ns[0] * nj[1] * nj[2] : 0;
+  const size_t need = wel * sizeof(double) + (t1 + t2) * sizeof(double2);
   if (need > dst->iws_bytes) {
     if (dst->d_iws) {
       HIPTRY(hipStreamSynchronize(dst->dv.stream));
@@ -1111,106 +1138,105 @@ sop_status sop_interpolate(const sop_plan* src, const void* psi_src, sop_plan* d
   // the source grid differs from the last call's
   double key[9];
   for (int a = 0; a < 3; ++a) {
-    key[3 * a] = (double)ns[a];
+    key[3 * a] = a < nax ? (double)src->n[a] : 1.0;
     key[3 * a + 1] = a < nax ? src->lo[a] : 0.0;
     key[3 * a + 2] = a < nax ? src->hi[a] : 0.0;
   }
   const bool reuse = dst->iws_valid && std::equal(key, key + 9, dst->iws_key);
-  double2* W[3];
-  double2* w = (double2*)dst->d_iws;
-  for (int a = 0; a < nax; ++a) {
-    W[a] = w;
-    w += (size_t)nd[a] * ns[a];
-  }
-  double2* T1 = w;
-  double2* T2 = w + t1;
+  double* const wbase = (double*)dst->d_iws;
+  double2* const T1 = (double2*)(wbase + wel);  // wel is a multiple of 128
+  double2* const T2 = T1 + t1;
   const DevView& d = dst->dv;
-  if (!reuse) {
+  if (!reuse && !empty) {
     dst->iws_valid = false;
-    sop::TimedLaunch tl(d, sop::KIND_OTHER, (double)wel * sizeof(double2));
-    for (int a = 0; a < nax; ++a)
-      HIPTRY(sop::interp_weights(d.stream, W[a], (int)ns[a], src->lo[a], src->hi[a],
-                                 (int)nd[a], dst->lo[a], dst->hi[a]));
+    sop::TimedLaunch tl(d, sop::KIND_OTHER, (double)wel * sizeof(double));
+    for (int a = a0; a < 3; ++a) {
+      const int i = a - a0;
+      if (share[a] != a) continue;
+      HIPTRY(sop::interp_weights(d.stream, wbase + woff[a], src->n[i], src->lo[i], src->hi[i],
+                                 dst->n[i], dst->lo[i], dst->hi[i], j0[a], nj[a], (int)ldw[a]));
+    }
     std::copy(key, key + 9, dst->iws_key);
     dst->iws_valid = true;
   }
-  auto flops = [](const sop::CgemmArgs& g, int batch) {
-    return 8.0 * g.M * (double)g.N * g.K * batch;
-  };
-  // Host check, before every launch, that the product's last elements lie
-  // inside the buffers it reads and writes.
-  auto fits = [](const sop::CgemmArgs& g, int batch, size_t na, size_t nb, size_t nc) {
-    const long long b = batch - 1, m = g.M - 1, n = g.N - 1, k = g.K - 1;
-    return (size_t)(b * g.bsa + m * g.sai + k * g.sak) < na &&
-           (size_t)(b * g.bsb + k * g.sbk + n * g.sbj) < nb &&
-           (size_t)(b * g.bsc + m * g.sci + n * g.scj) < nc;
-  };
   const size_t nsrc = (size_t)S * ns[0] * ns[1] * ns[2];
   const size_t ndst = (size_t)S * nd[0] * nd[1] * nd[2];
-  const int zax = nax - 1;  // the contiguous axis
-  {  // along z: rows of the source times W_z^T
-    sop::CgemmArgs g;
-    g.A = (const double2*)psi_src;
-    g.M = (int)(S * (nax == 3 ? ns[0] * ns[1] : 1));  // every line along z
-    g.K = (int)ns[zax];
-    g.N = (int)nd[zax];
-    g.sai = g.K;
-    g.sak = 1;
-    g.B = W[zax];
-    g.sbk = 1;
-    g.sbj = g.K;
-    g.C = nax == 3 ? T1 : (double2*)psi_dst;
-    g.sci = g.N;
-    g.scj = 1;
-    if (!fits(g, 1, nsrc, (size_t)nd[zax] * ns[zax], nax == 3 ? t1 : ndst))
-      return fail(SOP_ERR_INVALID, "interpolation: internal size check failed (z)");
-    sop::TimedLaunch tl(d, sop::KIND_INTERP, flops(g, 1));
-    HIPTRY(sop::cgemm(d.stream, g, 1));
+  // destination points outside the source box
+  sop::InterpZero zero;
+  zero.S = S;
+  for (int a = 0; a < 3; ++a) {
+    zero.n[a] = (int)nd[a];
+    zero.j0[a] = j0[a];
+    zero.nj[a] = empty ? 0 : nj[a];
   }
-  if (nax == 3) {
-    {  // along y: W_y times each (y, z) slab
-      sop::CgemmArgs g;
-      g.A = W[1];
-      g.M = (int)nd[1];
-      g.K = (int)ns[1];
-      g.N = (int)nd[2];
-      g.sai = g.K;
-      g.sak = 1;
-      g.B = T1;
-      g.sbk = nd[2];
-      g.sbj = 1;
-      g.bsb = ns[1] * nd[2];
-      g.C = T2;
-      g.sci = nd[2];
-      g.scj = 1;
-      g.bsc = nd[1] * nd[2];
-      const int batch = (int)(S * ns[0]);
-      if (!fits(g, batch, (size_t)nd[1] * ns[1], t1, t2))
-        return fail(SOP_ERR_INVALID, "interpolation: internal size check failed (y)");
-      sop::TimedLaunch tl(d, sop::KIND_INTERP, flops(g, batch));
-      HIPTRY(sop::cgemm(d.stream, g, batch));
-    }
-    {  // along x: W_x times each surface's (x, yz) matrix
-      sop::CgemmArgs g;
-      g.A = W[0];
-      g.M = (int)nd[0];
-      g.K = (int)ns[0];
-      g.N = (int)(nd[1] * nd[2]);
-      g.sai = g.K;
-      g.sak = 1;
-      g.B = T2;
-      g.sbk = nd[1] * nd[2];
-      g.sbj = 1;
-      g.bsb = ns[0] * nd[1] * nd[2];
-      g.C = (double2*)psi_dst;
-      g.sci = nd[1] * nd[2];
-      g.scj = 1;
-      g.bsc = nd[0] * nd[1] * nd[2];
-      if (!fits(g, S, (size_t)nd[0] * ns[0], t2, ndst))
-        return fail(SOP_ERR_INVALID, "interpolation: internal size check failed (x)");
-      sop::TimedLaunch tl(d, sop::KIND_INTERP, flops(g, S));
-      HIPTRY(sop::cgemm(d.stream, g, S));
-    }
+  if (empty || nj[0] < nd[0] || nj[1] < nd[1] || nj[2] < nd[2]) zero.out = (double2*)psi_dst;
+  if (zero.out) {
+    sop::TimedLaunch tl(d, sop::KIND_OTHER, 0.0);
+    HIPTRY(sop::interp_zero(d.stream, zero));
+    if (empty) return SOP_OK;
+  }
+  // real FP64 operations of one axis: a real matrix times complex columns
+  auto flops = [](double M, double K, double N) { return 4.0 * M * K * N; };
+  if (nax == 1) {
+    sop::TimedLaunch tl(d, sop::KIND_INTERP, flops(nj[2], ns[2], S));
+    HIPTRY(sop::interp_rows(d.stream, wbase + woff[2], (int)ldw[2], (int)ns[2], S, nj[2],
+                            (const double2*)psi_src, (double2*)psi_dst + j0[2], (int)nd[2]));
+    return SOP_OK;
+  }
+  // Host check, before every launch, that the product's last elements lie
+  // inside the buffers it reads and writes.
+  auto run = [&](sop::InterpAxis& g, int a, bool krow, size_t nx, size_t nc) -> sop_status {
+    g.Wt = wbase + woff[a];
+    g.ldw = (int)ldw[a];
+    g.M = nj[a];
+    g.K = (int)ns[a];
+    const long long b = g.batch - 1, m = g.M - 1, k = g.K - 1, n = g.N - 1;
+    const long long lx = b * g.bsx + (krow ? n * g.K + k : k * g.ldx + n);
+    const long long lc = b * g.bsc + (krow ? n * g.ldc + m
+                                           : m * g.ldc + n / g.cdiv * g.crow +
+                                                 std::min<long long>(g.cdiv - 1, n));
+    if (lx < 0 || lc < 0 || (size_t)lx >= nx || (size_t)lc >= nc)
+      return fail(SOP_ERR_INVALID, "interpolation: internal size check failed");
+    sop::TimedLaunch tl(d, sop::KIND_INTERP, flops(g.M, g.K, (double)g.N * g.batch));
+    HIPTRY(sop::interp_axis(d.stream, g, krow));
+    return SOP_OK;
+  };
+  sop_status st;
+  {  // along z: T1[line][j] from every line of the source
+    sop::InterpAxis g;
+    g.X = (const double2*)psi_src;
+    g.N = (int)(S * ns[0] * ns[1]);
+    g.C = T1;
+    g.ldc = nj[2];
+    if ((st = run(g, 2, true, nsrc, t1)) != SOP_OK) return st;
+  }
+  {  // along y: each (surface, x) slab
+    sop::InterpAxis g;
+    g.X = T1;
+    g.N = nj[2];
+    g.batch = (int)(S * ns[0]);
+    g.ldx = nj[2];
+    g.bsx = ns[1] * nj[2];
+    g.C = T2;
+    g.ldc = nj[2];
+    g.bsc = (long long)nj[1] * nj[2];
+    g.cdiv = nj[2];
+    if ((st = run(g, 1, false, t1, t2)) != SOP_OK) return st;
+  }
+  {  // along x: each surface's (x, yz) matrix, into the destination's box
+    sop::InterpAxis g;
+    g.X = T2;
+    g.N = nj[1] * nj[2];
+    g.batch = S;
+    g.ldx = (long long)nj[1] * nj[2];
+    g.bsx = ns[0] * (long long)nj[1] * nj[2];
+    const size_t off = ((size_t)j0[0] * nd[1] + j0[1]) * nd[2] + j0[2];
+    g.C = (double2*)psi_dst + off;
+    g.ldc = nd[1] * nd[2];
+    g.bsc = nd[0] * nd[1] * nd[2];
+    g.cdiv = nj[2];
+    g.crow = nd[2];
+    if ((st = run(g, 0, false, t2, ndst - off)) != SOP_OK) return st;
   }
   return SOP_OK;
 }

@@ -163,3 +163,42 @@ def test_matrices_follow_the_source_grid(torch_cuda, orc):
         err = rel_l2(got, ref)
         print(f"[interp source switch] rel L2 {err:.2e}")
         assert err < TOL
+
+
+@pytest.mark.parametrize("na,nb,box", [
+    (32, 32, [(-2.0, 5.0), (-7.0, 7.0), (-9.9, 9.9)]),    # 17, 32 and 23 rows: one 32-row tile
+    (32, 48, [(-7.0, 7.0), (-12.0, 3.0), (6.9, 30.0)]),   # 48, 32 and one row
+    (48, 64, [(-7.1, 7.1), (-8.0, 9.0), (-7.0, 6.9)]),    # 64-row tiles, odd column counts
+    (32, 128, [(-8.0, 7.5), (-7.0, 7.0), (-20.0, 20.0)]),  # 128-row and 64-row tiles
+    (64, 32, [(8.0, 9.0), (-7.0, 7.0), (-7.0, 7.0)]),     # no point inside: zeros
+])
+def test_axes_of_different_boxes(torch_cuda, orc, na, nb, box):
+    """Destination boxes that differ by axis, so that each axis has its own
+    interval of points inside the source box (tile remainders, one row, none).
+    Tolerance: as above; at most 64 terms of rounding 1.1e-16 a product axis,
+    three axes, against sums of the same size."""
+    torch = torch_cuda
+    ma = synth.lvc_3d(n=na)
+    mb = synth.lvc_3d(n=nb)
+    mb.lo, mb.hi = [b[0] for b in box], [b[1] for b in box]
+    psi = synth.random_state(ma.psi0.shape, seed=5)
+    got = gpu_interp(torch, ma, psi, mb)
+    ref = oracle_interp(orc, psi, ma, mb)
+    if not ref.any():
+        assert not got.any()
+        return
+    assert np.array_equal(got == 0, ref == 0)  # the zero points are the same ones
+    err = rel_l2(got, ref)
+    print(f"[interp {na}->{nb} {box}] rel L2 {err:.2e}")
+    assert err < TOL
+
+
+@pytest.mark.parametrize("na,nb,S", [(16, 2048, 1), (2048, 16, 2), (128, 64, 1), (512, 1024, 2)])
+def test_1d_rows(torch_cuda, orc, na, nb, S):
+    torch = torch_cuda
+    ma = synth.random_small([na], S, seed=6, lo=-5.0, hi=5.0)
+    mb = synth.random_small([nb], S, seed=7, lo=-6.0, hi=4.5)
+    psi = synth.random_state(ma.psi0.shape, seed=8)
+    err = rel_l2(gpu_interp(torch, ma, psi, mb), oracle_interp(orc, psi, ma, mb))
+    print(f"[interp rows {na}->{nb} S={S}] rel L2 {err:.2e}")
+    assert err < TOL
