@@ -20,87 +20,125 @@
 namespace sop {
 namespace {
 
-// One sweep set of cyclic Jacobi rotations on a real symmetric S x S matrix.
-// On return A is diagonal (eigenvalues on the diagonal) and R holds the
-// eigenvectors in its columns.  Each rotation's cosine and sine come from
-// the smaller root t = tan(theta) of t^2 + 2 zeta t - 1 = 0, zeta =
-// (a_qq - a_pp) / (2 a_pq) (the symmetric Schur step of Golub and Van Loan,
-// Matrix Computations, Sec. 8.5): t = sign(zeta) / (|zeta| + sqrt(1 +
-// zeta^2)), c = 1 / sqrt(1 + t^2), s = t c -- the rotation with
-// tan(2 theta) = 2 a_pq / (a_qq - a_pp), |theta| <= pi/4, without a
-// trigonometric call.
+// 1/sqrt(x) for a normal x: the hardware's estimate (about 24 bits) and one
+// third-order step, e = 1 - x y^2, y (1 + e/2 + 3 e^2/8): what is left is that
+// step's rounding.  (The general square root and division spend most of their
+// instructions on scaling and special cases.)
+__device__ __forceinline__ double rsqrt_short(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  const double e = fma(-(x * y), y, 1.0);
+  return fma(y * e, fma(0.375, e, 0.5), y);
+}
+
+// Cyclic Jacobi rotations on a real symmetric S x S matrix (the upper
+// triangle of A is used).  On return A is diagonal (eigenvalues on the
+// diagonal) and R holds the eigenvectors in its columns.  Each rotation has
+// tan(2 theta) = 2 a_pq / (a_qq - a_pp), |theta| <= pi/4 (the symmetric Schur
+// step of Golub and Van Loan, Matrix Computations, Sec. 8.5), from two inverse
+// square roots: with d = a_qq - a_pp, b = 2 a_pq sign(d) and y = 1/sqrt(d^2 + b^2),
+//   cos 2 theta = |d| y,  sin 2 theta = b y,  1/c = 1/sqrt((1 + cos 2 theta)/2),
+//   s = sin 2 theta / (2 c),  tan theta = s / c,
+// and a_pp - t a_pq, a_qq + t a_pq on the diagonal.  The matrix is first
+// scaled by the power of two that brings its largest entry to [1/2, 1), so
+// that d^2 + b^2 neither overflows nor, with entries below 1e-150 of the
+// largest taken as zero, underflows.
+// The formation is bound by FP64 issue, then by its bytes: k_form_eigq at
+// 128^3 x 3 with three couplings took 147 us with general divisions and
+// square roots (three and two a rotation) and two-sided updates of the full
+// matrix, and takes 80 us (44 us with one coupling, 5.4 TB/s).
 template <int S>
-__device__ void jacobi_sym(double (&A)[S][S], double (&R)[S][S]) {
+__device__ __forceinline__ void jacobi_sym(double (&A)[S][S], double (&R)[S][S]) {
 #pragma unroll
   for (int i = 0; i < S; ++i)
 #pragma unroll
     for (int j = 0; j < S; ++j) R[i][j] = (i == j) ? 1.0 : 0.0;
   if constexpr (S == 1) return;
+  double big = 0.0;
+#pragma unroll
+  for (int i = 0; i < S; ++i)
+#pragma unroll
+    for (int j = i; j < S; ++j) big = fmax(big, fabs(A[i][j]));
+  const int ex = __builtin_amdgcn_frexp_exp(big);
+#pragma unroll
+  for (int i = 0; i < S; ++i)
+#pragma unroll
+    for (int j = i; j < S; ++j) A[i][j] = __builtin_amdgcn_ldexp(A[i][j], -ex);
   for (int sweep = 0; sweep < 24; ++sweep) {
     bool rotated = false;
 #pragma unroll
     for (int p = 0; p < S - 1; ++p) {
 #pragma unroll
       for (int q = p + 1; q < S; ++q) {
-        const double apq = A[p][q];
-        if (apq == 0.0) continue;
-        const double scale = fabs(A[p][p]) + fabs(A[q][q]);
-        if (fabs(apq) <= 1e-18 * scale) {  // negligible next to the diagonal
+        const double apq = A[p][q], app = A[p][p], aqq = A[q][q];
+        // negligible next to the diagonal or to the whole matrix
+        if (fabs(apq) <= fmax(1e-18 * (fabs(app) + fabs(aqq)), 1e-150)) {
           A[p][q] = 0.0;
-          A[q][p] = 0.0;
           continue;
         }
         rotated = true;
-        const double zeta = (A[q][q] - A[p][p]) / (2.0 * apq);
-        // 1 / (|zeta| + sqrt(1 + zeta^2)) without overflow for huge zeta
-        const double az = fabs(zeta);
-        const double tt = az > 1e150 ? 0.5 / az : 1.0 / (az + sqrt(1.0 + az * az));
-        const double tn = zeta < 0.0 ? -tt : tt;
-        const double cs = 1.0 / sqrt(1.0 + tn * tn);
-        const double sn = tn * cs;
-        // A <- A J (columns p, q), J = [[c, s], [-s, c]] on (p, q)
-#pragma unroll
-        for (int r = 0; r < S; ++r) {
-          const double arp = A[r][p], arq = A[r][q];
-          A[r][p] = cs * arp - sn * arq;
-          A[r][q] = sn * arp + cs * arq;
-          const double rrp = R[r][p], rrq = R[r][q];
-          R[r][p] = cs * rrp - sn * rrq;
-          R[r][q] = sn * rrp + cs * rrq;
+        const double d = aqq - app;
+        const double b = d < 0.0 ? -2.0 * apq : 2.0 * apq;
+        double c, s, t;
+        if constexpr (S == 2) {
+          // one rotation a point, the kernel waits for memory: correctly
+          // rounded roots and quotients, t = b / (|d| + sqrt(d^2 + b^2))
+          t = b / (fabs(d) + sqrt(fma(d, d, b * b)));
+          c = 1.0 / sqrt(fma(t, t, 1.0));
+          s = t * c;
+        } else {
+          const double y = rsqrt_short(fma(d, d, b * b));
+          const double c2 = fma(0.5 * fabs(d), y, 0.5);  // cos^2 theta, in [1/2, 1]
+          const double ci = rsqrt_short(c2);
+          c = c2 * ci;
+          s = (0.5 * (b * y)) * ci;
+          t = s * ci;
         }
-        // A <- J^T A (rows p, q)
-#pragma unroll
-        for (int r = 0; r < S; ++r) {
-          const double apr = A[p][r], aqr = A[q][r];
-          A[p][r] = cs * apr - sn * aqr;
-          A[q][r] = sn * apr + cs * aqr;
-        }
+        A[p][p] = fma(-t, apq, app);
+        A[q][q] = fma(t, apq, aqq);
         A[p][q] = 0.0;
-        A[q][p] = 0.0;
+#pragma unroll
+        for (int r = 0; r < S; ++r) {
+          if (r != p && r != q) {
+            double& arp = r < p ? A[r][p] : A[p][r];
+            double& arq = r < q ? A[r][q] : A[q][r];
+            const double vp = arp, vq = arq;
+            arp = fma(c, vp, -(s * vq));
+            arq = fma(s, vp, c * vq);
+          }
+          const double rp = R[r][p], rq = R[r][q];
+          R[r][p] = fma(c, rp, -(s * rq));
+          R[r][q] = fma(s, rp, c * rq);
+        }
       }
     }
     if (!rotated) break;
   }
+#pragma unroll
+  for (int i = 0; i < S; ++i) A[i][i] = __builtin_amdgcn_ldexp(A[i][i], ex);
 }
 
 // Destination index of (table u, entry e, point x): structure of arrays for
-// 1D (tile = 0) or the z-pass tile layout for a cubic 3D grid of side n.
+// 1D (tile = 0) or the z-pass tile layout for a cubic 3D grid of side n
+// (x below 2^31: 32-bit divisions).
 __device__ __forceinline__ int64_t table_index(int64_t npts, int NE, int tile, int n, int u, int e,
                                                int64_t x) {
   if (tile == 0) return ((int64_t)u * NE + e) * npts + x;
-  const int64_t plane = (int64_t)n * n;
-  const int64_t z = x / plane, y = (x / n) % n, xx = x % n;
-  const int64_t tl = y * (n / tile) + xx / tile;
-  return (int64_t)u * NE * npts + tl * ((int64_t)n * NE * tile) + (z * NE + e) * tile + xx % tile;
+  const uint32_t row = (uint32_t)x / (uint32_t)n, xx = (uint32_t)x - row * (uint32_t)n;
+  const uint32_t z = row / (uint32_t)n, y = row - z * (uint32_t)n;
+  const uint32_t tx = xx / (uint32_t)tile;
+  const uint32_t tl = y * ((uint32_t)n / (uint32_t)tile) + tx;
+  return (int64_t)u * NE * npts + (int64_t)tl * ((int64_t)n * NE * tile) +
+         ((int64_t)z * NE + e) * tile + (xx - tx * (uint32_t)tile);
 }
 
 template <typename T, int S>
 __global__ void __launch_bounds__(256)
     k_form_vexp(const double* __restrict__ vraw, int64_t npts, const double* __restrict__ taus,
                 int ntau, int tile, int n, cx<T>* __restrict__ out,
-                const double* __restrict__ dtab, const double* __restrict__ s_dev) {
+                const double* __restrict__ dtab, unsigned dmask,
+                const double* __restrict__ s_dev) {
   constexpr int NE = S * (S + 1) / 2;
-  const double sd = dtab ? *s_dev : 0.0;  // driven: V = vraw + s D
+  const double sd = dmask ? *s_dev : 0.0;  // driven: V = vraw + s D
   for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < npts;
        x += (int64_t)gridDim.x * blockDim.x) {
     double A[S][S], R[S][S];
@@ -110,7 +148,7 @@ __global__ void __launch_bounds__(256)
 #pragma unroll
       for (int j = i; j < S; ++j) {
         const int64_t o = (int64_t)e * npts + x;
-        const double vij = dtab ? vraw[o] + sd * dtab[o] : vraw[o];
+        const double vij = (dmask >> e) & 1 ? vraw[o] + sd * dtab[o] : vraw[o];
         A[i][j] = vij;
         A[j][i] = vij;
         ++e;
@@ -289,17 +327,16 @@ __global__ void __launch_bounds__(kReduceThreads)
 // z-pass tile layout: S = 3 as the unit quaternion (w, x) (y, z) of R and
 // (lam_0, lam_1) (lam_2, 0); S = 2 as (cos, sin) of the rotation angle and
 // (lam_0, lam_1).  One table serves every coefficient: each potential
-// action forms exp(-i tau lam) itself.  The quaternion comes from the
-// largest of w^2, x^2, y^2, z^2 (each = (1 +- R_00 +- R_11 +- R_22)/4), so
-// the division is always by a number >= 1/2.
+// action forms exp(-i tau lam) itself.  The quaternion is the row of products
+// with its largest component (largest of w^2, x^2, y^2, z^2, each =
+// (1 +- R_00 +- R_11 +- R_22)/4), scaled to unit length.
 template <int S>
 __global__ void __launch_bounds__(256)
     k_form_eigq(const double* __restrict__ vraw, int64_t npts, int tile, int n,
-                cx<double>* __restrict__ out, const double* __restrict__ dtab,
+                cx<double>* __restrict__ out, const double* __restrict__ dtab, unsigned dmask,
                 const double* __restrict__ s_dev) {
-  constexpr int NE = S * (S + 1) / 2;
   constexpr int NQ = eig_slots(S);
-  const double sd = dtab ? *s_dev : 0.0;  // driven: V = vraw + s D
+  const double sd = dmask ? *s_dev : 0.0;  // driven: V = vraw + s D
   for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < npts;
        x += (int64_t)gridDim.x * blockDim.x) {
     double A[S][S], R[S][S];
@@ -309,7 +346,7 @@ __global__ void __launch_bounds__(256)
 #pragma unroll
       for (int j = i; j < S; ++j) {
         const int64_t o = (int64_t)e * npts + x;
-        const double vij = dtab ? vraw[o] + sd * dtab[o] : vraw[o];
+        const double vij = (dmask >> e) & 1 ? vraw[o] + sd * dtab[o] : vraw[o];
         A[i][j] = vij;
         A[j][i] = vij;
         ++e;
@@ -324,33 +361,19 @@ __global__ void __launch_bounds__(256)
       const double t1 = 1.0 + R[0][0] - R[1][1] - R[2][2];  // 4 x^2
       const double t2 = 1.0 - R[0][0] + R[1][1] - R[2][2];  // 4 y^2
       const double t3 = 1.0 - R[0][0] - R[1][1] + R[2][2];  // 4 z^2
-      double w, qx, qy, qz;
-      if (t0 >= t1 && t0 >= t2 && t0 >= t3) {
-        const double r = 2.0 * sqrt(t0);  // 4 w
-        w = 0.25 * r;
-        qx = (R[2][1] - R[1][2]) / r;
-        qy = (R[0][2] - R[2][0]) / r;
-        qz = (R[1][0] - R[0][1]) / r;
-      } else if (t1 >= t2 && t1 >= t3) {
-        const double r = 2.0 * sqrt(t1);  // 4 x
-        w = (R[2][1] - R[1][2]) / r;
-        qx = 0.25 * r;
-        qy = (R[0][1] + R[1][0]) / r;
-        qz = (R[0][2] + R[2][0]) / r;
-      } else if (t2 >= t3) {
-        const double r = 2.0 * sqrt(t2);  // 4 y
-        w = (R[0][2] - R[2][0]) / r;
-        qx = (R[0][1] + R[1][0]) / r;
-        qy = 0.25 * r;
-        qz = (R[1][2] + R[2][1]) / r;
-      } else {
-        const double r = 2.0 * sqrt(t3);  // 4 z
-        w = (R[1][0] - R[0][1]) / r;
-        qx = (R[0][2] + R[2][0]) / r;
-        qy = (R[1][2] + R[2][1]) / r;
-        qz = 0.25 * r;
-      }
-      const double nrm = 1.0 / sqrt(w * w + qx * qx + qy * qy + qz * qz);
+      // 4 times the products with the largest component, chosen without
+      // branches: (w^2, wx, wy, wz), (wx, x^2, xy, xz), ..
+      const double wx = R[2][1] - R[1][2], wy = R[0][2] - R[2][0], wz = R[1][0] - R[0][1];
+      const double xy = R[0][1] + R[1][0], xz = R[0][2] + R[2][0], yz = R[1][2] + R[2][1];
+      const bool b0 = t0 >= t1 && t0 >= t2 && t0 >= t3;
+      const bool b1 = !b0 && t1 >= t2 && t1 >= t3;
+      const bool b2 = !b0 && !b1 && t2 >= t3;
+      double w = b0 ? t0 : b1 ? wx : b2 ? wy : wz;
+      double qx = b0 ? wx : b1 ? t1 : b2 ? xy : xz;
+      double qy = b0 ? wy : b1 ? xy : b2 ? t2 : yz;
+      double qz = b0 ? wz : b1 ? xz : b2 ? yz : t3;
+      // scaled to a unit quaternion (the largest product is at least 1)
+      const double nrm = rsqrt_short(fma(w, w, fma(qx, qx, fma(qy, qy, qz * qz))));
       slot[0] = cx<double>{w * nrm, qx * nrm};
       slot[1] = cx<double>{qy * nrm, qz * nrm};
       slot[2] = cx<double>{A[0][0], A[1][1]};
@@ -358,7 +381,6 @@ __global__ void __launch_bounds__(256)
     }
 #pragma unroll
     for (int q = 0; q < NQ; ++q) out[table_index(npts, NQ, tile, n, 0, q, x)] = slot[q];
-    (void)NE;
   }
 }
 
@@ -455,11 +477,11 @@ __global__ void __launch_bounds__(kReduceThreads)
 
 template <int S, typename T>
 hipError_t form_impl(const DevView& d, const double* vraw, const double* taus, int ntau, int tile,
-                     void* out, const double* dtab, const double* s_dev) {
+                     void* out, const double* dtab, unsigned dmask, const double* s_dev) {
   int blocks = (int)((d.npts + 255) / 256);
   if (blocks > 4096) blocks = 4096;
   hipLaunchKernelGGL((k_form_vexp<T, S>), dim3(blocks), dim3(256), 0, d.stream, vraw, d.npts,
-                     taus, ntau, tile, d.n[0], (cx<T>*)out, dtab, s_dev);
+                     taus, ntau, tile, d.n[0], (cx<T>*)out, dtab, dmask, s_dev);
   return hipGetLastError();
 }
 
@@ -474,26 +496,26 @@ hipError_t obs_points_impl(const DevView& d, const void* psi, const double* vraw
 }  // namespace
 
 hipError_t form_vexp(const DevView& d, const double* vraw_dev, const double* taus, int ntau,
-                     int tile, void* out, const double* dtab, const double* s_dev) {
+                     int tile, void* out, const double* dtab, unsigned dmask, const double* s_dev) {
   switch (d.S) {
-    case 1: return d.f64 ? form_impl<1, double>(d, vraw_dev, taus, ntau, tile, out, dtab, s_dev)
-                         : form_impl<1, float>(d, vraw_dev, taus, ntau, tile, out, dtab, s_dev);
-    case 2: return d.f64 ? form_impl<2, double>(d, vraw_dev, taus, ntau, tile, out, dtab, s_dev)
-                         : form_impl<2, float>(d, vraw_dev, taus, ntau, tile, out, dtab, s_dev);
-    case 3: return d.f64 ? form_impl<3, double>(d, vraw_dev, taus, ntau, tile, out, dtab, s_dev)
-                         : form_impl<3, float>(d, vraw_dev, taus, ntau, tile, out, dtab, s_dev);
+    case 1: return d.f64 ? form_impl<1, double>(d, vraw_dev, taus, ntau, tile, out, dtab, dmask, s_dev)
+                         : form_impl<1, float>(d, vraw_dev, taus, ntau, tile, out, dtab, dmask, s_dev);
+    case 2: return d.f64 ? form_impl<2, double>(d, vraw_dev, taus, ntau, tile, out, dtab, dmask, s_dev)
+                         : form_impl<2, float>(d, vraw_dev, taus, ntau, tile, out, dtab, dmask, s_dev);
+    case 3: return d.f64 ? form_impl<3, double>(d, vraw_dev, taus, ntau, tile, out, dtab, dmask, s_dev)
+                         : form_impl<3, float>(d, vraw_dev, taus, ntau, tile, out, dtab, dmask, s_dev);
     default: return hipErrorInvalidValue;
   }
 }
 
 hipError_t form_eigq(const DevView& d, const double* vraw_dev, int tile, void* out,
-                     const double* dtab, const double* s_dev) {
+                     const double* dtab, unsigned dmask, const double* s_dev) {
   int blocks = (int)((d.npts + 255) / 256);
   if (blocks > 4096) blocks = 4096;
   cx<double>* o = (cx<double>*)out;
   switch (d.S) {
-    case 2: hipLaunchKernelGGL(k_form_eigq<2>, dim3(blocks), dim3(256), 0, d.stream, vraw_dev, d.npts, tile, d.n[0], o, dtab, s_dev); break;
-    case 3: hipLaunchKernelGGL(k_form_eigq<3>, dim3(blocks), dim3(256), 0, d.stream, vraw_dev, d.npts, tile, d.n[0], o, dtab, s_dev); break;
+    case 2: hipLaunchKernelGGL(k_form_eigq<2>, dim3(blocks), dim3(256), 0, d.stream, vraw_dev, d.npts, tile, d.n[0], o, dtab, dmask, s_dev); break;
+    case 3: hipLaunchKernelGGL(k_form_eigq<3>, dim3(blocks), dim3(256), 0, d.stream, vraw_dev, d.npts, tile, d.n[0], o, dtab, dmask, s_dev); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -548,7 +570,7 @@ hipError_t form_eig(const DevView& d, const double* vraw_dev, int tile, void* ou
     case 1: hipLaunchKernelGGL(k_form_eig<1>, dim3(blocks), dim3(256), 0, d.stream, vraw_dev, d.npts, tile, d.n[0], (cx<double>*)out); break;
     // two and three surfaces: the compact eigen form (rotation and eigenvalues)
     case 2:
-    case 3: return form_eigq(d, vraw_dev, tile, out, nullptr, nullptr);
+    case 3: return form_eigq(d, vraw_dev, tile, out);
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();

@@ -253,6 +253,7 @@ struct sop_plan {
   std::vector<double> theta;  // host copy of the current parameters
   double* d_drive = nullptr;  // drive samples of sop_propagate_driven
   size_t drive_cap = 0;       // doubles held by d_drive
+  unsigned dmask = 0;         // packed entries of dvtables[0] that are not zero everywhere
   void* d_eig = nullptr;      // adjoint eigen table (FP64, tile layout)
   double* d_w = nullptr;      // [S] adjoint weights
   sop::GraphCache* graphs = nullptr;
@@ -347,14 +348,39 @@ double gershgorin_bound(const double* v, int S, int64_t npts) {
       idx[(size_t)j * S + i] = e;
       ++e;
     }
-  double b = 0.0;
-  for (int64_t x = 0; x < npts; ++x)
+  // running maxima of a block of points, entry by entry (contiguous reads,
+  // elementwise arithmetic), reduced once at the end
+  constexpr int kBlock = 512;
+  std::vector<double> best(kBlock, 0.0), row(kBlock);
+  for (int64_t x0 = 0; x0 < npts; x0 += kBlock) {
+    const int m = (int)std::min<int64_t>(kBlock, npts - x0);
     for (int i = 0; i < S; ++i) {
-      double r = 0.0;
-      for (int j = 0; j < S; ++j) r += std::fabs(v[(int64_t)idx[(size_t)i * S + j] * npts + x]);
-      b = std::max(b, r);
+      std::fill(row.begin(), row.end(), 0.0);
+      for (int j = 0; j < S; ++j) {
+        const double* const e0 = v + (int64_t)idx[(size_t)i * S + j] * npts + x0;
+        for (int x = 0; x < m; ++x) row[x] += std::fabs(e0[x]);
+      }
+      for (int x = 0; x < m; ++x) best[x] = best[x] < row[x] ? row[x] : best[x];
     }
+  }
+  double b = 0.0;
+  for (double r : best) b = std::max(b, r);
   return b;
+}
+
+// Bit e set where entry e of a packed [ne][npts] table is not zero everywhere.
+unsigned entry_mask(const double* v, int ne, int64_t npts) {
+  unsigned mask = 0;
+  for (int e = 0; e < ne; ++e) {
+    const double* const t = v + (int64_t)e * npts;
+    for (int64_t x0 = 0; x0 < npts && !((mask >> e) & 1); x0 += 4096) {
+      const int64_t m = std::min<int64_t>(4096, npts - x0);
+      int any = 0;
+      for (int64_t x = 0; x < m; ++x) any |= t[x0 + x] != 0.0;  // NaN counts
+      if (any) mask |= 1u << e;
+    }
+  }
+  return mask;
 }
 
 // Whether every phase the eigen-form z-pass forms, tau lam with tau up to
@@ -649,6 +675,8 @@ sop_status sop_plan_create_with_allocator(const sop_plan_desc* desc, void* hip_s
     d.graphs = p->graphs;
   }
   p->nparams = desc->nparams;
+  // a driven run reads only the entries its one parameter table has
+  if (p->nparams == 1) p->dmask = entry_mask(desc->dvtables, NE, p->npts);
   if (p->nparams > 0) {
     const size_t dvb = (size_t)p->nparams * vbytes;
     if (dalloc(p, &p->d_vbase, vbytes) != hipSuccess || dalloc(p, &p->d_dv, dvb) != hipSuccess ||
@@ -1361,9 +1389,9 @@ sop_status sop_propagate_driven(sop_plan* p, void* psi, int64_t nsteps, const do
   d.nact = 1;
   const size_t tab =
       (size_t)(p->S * (p->S + 1) / 2) * p->npts * p->csize * (p->dtype == SOP_C128 ? 1 : 2);
-  // formation bytes per potential action: V0 and D read, the table written
+  // formation bytes per potential action: V0 and D's entries read, the table written
   const double fbytes =
-      (2.0 * (p->S * (p->S + 1) / 2) * sizeof(double) +
+      ((p->S * (p->S + 1) / 2 + __builtin_popcount(p->dmask)) * (double)sizeof(double) +
        (p->eig_form ? sop::eig_slots(p->S) * 16.0 : (double)tab / (double)p->npts)) *
       (double)p->npts;
   const int nact = (int)p->dv.hprog.size();
@@ -1382,11 +1410,13 @@ sop_status sop_propagate_driven(sop_plan* p, void* psi, int64_t nsteps, const do
         const double* s_dev = p->d_drive + (size_t)n * nv + v++;
         sop::TimedLaunch tl(d, sop::KIND_OTHER, fbytes);
         if (p->eig_form) {
-          HIPTRY(sop::form_eigq(d, p->d_vbase, p->tile, p->d_vexp, p->d_dv, s_dev));
+          HIPTRY(sop::form_eigq(d, p->d_vbase, p->tile, p->d_vexp, p->d_dv, p->dmask,
+                                s_dev));
         } else {  // only the table this action reads
           const int idx = code & 0xffff;
           HIPTRY(sop::form_vexp(d, p->d_vbase, p->d_taus + idx, 1, p->tile,
-                                (char*)p->d_vexp + (size_t)idx * tab, p->d_dv, s_dev));
+                                (char*)p->d_vexp + (size_t)idx * tab, p->d_dv, p->dmask,
+                                s_dev));
         }
         if (a + 1 < nact && (p->dv.hprog[a + 1] >> 16) == sop::OP_T) na = 2;
       }
