@@ -136,7 +136,7 @@ typedef struct {
   int n_t_tables; /* stored kinetic factor sets                             */
   int64_t npts;
   size_t table_bytes;   /* device bytes of stored evolution operators      */
-  size_t scratch_bytes; /* device bytes of observables scratch             */
+  size_t scratch_bytes; /* bytes of one state: a bound of the observables' scratch */
 } sop_plan_info;
 
 typedef struct sop_plan sop_plan;
@@ -235,9 +235,9 @@ sop_status sop_propagate_many(sop_plan* plan, void* psi_dev, int count, int64_t 
 /* Observables of psi in FP64 (Sec. "Geometric properties of the exact
  * evolution operator"): out[0] = <psi|psi>, out[1] = <psi|H|psi>,
  * out[2+s] = population of surface s (s < nsurf), out[2+S] = <T>,
- * out[3+S] = <V>.  Inner products carry the volume element.  <T> is taken
- * in the momentum representation from an FFT of a scratch copy; psi is not
- * modified.  out must hold 4 + nsurf doubles (host).  Synchronises. */
+ * out[3+S] = <V>.  Inner products carry the volume element.  <T> is the sum
+ * over the axes of <T_d>, each taken in the momentum representation of its
+ * own axis; psi is only read.  out must hold 4 + nsurf doubles (host).  Synchronises. */
 sop_status sop_observables(sop_plan* plan, const void* psi_dev, double* out);
 
 /* <psi|phi> with the volume element; out[0] = Re, out[1] = Im (host).

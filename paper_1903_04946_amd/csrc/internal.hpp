@@ -156,7 +156,10 @@ struct TimedLaunch {
 bool k1d_supported(int n, int S);
 // count states [count][S][N] of the same plan, one workgroup each
 hipError_t k1d_propagate(const DevView& d, void* psi, int64_t nsteps, int conj, int count = 1);
-hipError_t k1d_fft_forward(const DevView& d, void* psi);
+// Raw sums of one state into out[S + 2] (device-visible): |psi_s|^2, psi^dag V
+// psi, and ck sum k^2 |F psi|^2 over the signed frequencies.
+hipError_t k1d_observe(const DevView& d, const void* psi, const double* vraw, double ck,
+                       double* out);
 
 // Device buffers of an adjoint sweep (FP64 only).
 struct AdjointView {
@@ -180,7 +183,11 @@ hipError_t k3d_adjoint_backward(const DevView& d, const AdjointView& a, int64_t 
 int k3d_table_tile(int n, bool f64);
 hipError_t k3d_propagate(const DevView& d, void* psi, int64_t nsteps, int conj);
 bool k3d_plane(int n, bool f64);  // the xy plane of an n^3 grid fits in LDS
-hipError_t k3d_fft_forward(const DevView& d, void* psi);
+// The same on 3D grids, with the weights c[axis] of each axis' transform;
+// part: k3d_obs_partials doubles.
+size_t k3d_obs_partials(int n, int S, bool f64);
+hipError_t k3d_observe(const DevView& d, const void* psi, const double* vraw, const double* c,
+                       double* part, double* out);
 
 // Complex double slots per point of the compact eigen form (3D, S = 2, 3).
 constexpr int eig_slots(int S) { return S == 3 ? 4 : 2; }
@@ -300,9 +307,6 @@ hipError_t form_vexp(const DevView& d, const double* vraw_dev, const double* tau
                      int tile, void* out,
                      const double* dtab = nullptr, unsigned dmask = 0,
                      const double* s_dev = nullptr);
-hipError_t obs_reduce(const DevView& d, const void* psi, const void* psi_hat,
-                      const double* vraw_dev, const double* inv_mass, const double* dx,
-                      double hbar, double* partials_dev, double* out_dev);
 hipError_t overlap_reduce(const DevView& d, const void* psi, const void* phi,
                           double* partials_dev, double* out_dev);
 hipError_t distance_reduce(const DevView& d, const void* psi, const void* phi,

@@ -2,6 +2,7 @@
 // inside one persistent workgroup per wavepacket (the step body is run_1d).
 #include "body_1d.hpp"
 #include "body_1d_w4.hpp"
+#include "reduce.hpp"
 
 namespace sop {
 namespace {
@@ -32,27 +33,69 @@ __global__ void __launch_bounds__(w4::kThreads)
   run_1d_w4<T>(psi, vexp, kin, tw, prog, nact, nsteps, conj, lds);
 }
 
-// Forward transform of every surface (natural order in and out), used for
-// the kinetic energy.
+// Observables of one state in one workgroup: out[0..S) = sum |psi_s|^2,
+// out[S] = sum psi^dag V psi, out[S + 1] = ck sum k^2 |F psi|^2 (k signed; FP64
+// sums in a fixed order).
 template <typename T, class SC, int S>
 __global__ void __launch_bounds__(SC::TPC)
-    k1d_fft_kernel(cx<T>* __restrict__ psi, const cx<T>* __restrict__ tw) {
+    k1d_obs_kernel(const cx<T>* __restrict__ psi, const double* __restrict__ vraw,
+                   const cx<T>* __restrict__ tw, double ck, double* __restrict__ out) {
   extern __shared__ char smem_raw[];
   cx<T>* lds = reinterpret_cast<cx<T>*>(smem_raw);
   constexpr int N = SC::N, E = SC::E;
   const int t = threadIdx.x;
-  cx<T> v[1][E];
+  cx<T> v[S][E];
+#pragma unroll
+  for (int s = 0; s < S; ++s)
+#pragma unroll
+    for (int q = 0; q < E; ++q) v[s][q] = psi[s * N + own_idx<N, E, SC::RF>(t, q)];
+  double acc[S + 2];
+#pragma unroll
+  for (int k = 0; k < S + 2; ++k) acc[k] = 0.0;
+#pragma unroll
+  for (int q = 0; q < E; ++q) {
+    const int x = own_idx<N, E, SC::RF>(t, q);
+    int e = 0;
+#pragma unroll
+    for (int i = 0; i < S; ++i)
+#pragma unroll
+      for (int j = i; j < S; ++j) {
+        // Re(conj(psi_i) psi_j), counted twice off the diagonal
+        const double rr = (double)v[i][q].re * (double)v[j][q].re +
+                          (double)v[i][q].im * (double)v[j][q].im;
+        if (i == j) acc[i] += rr;
+        acc[S] += (i == j ? 1.0 : 2.0) * vraw[(size_t)e * N + x] * rr;
+        ++e;
+      }
+  }
   const LayPadded lay{0, lds_pencil<SC>()};
+  double a = 0.0;
+#pragma unroll
   for (int s = 0; s < S; ++s) {
+    fft_forward<SC, 1>(v + s, lds, lay, tw, t);
 #pragma unroll
-    for (int q = 0; q < E; ++q) v[0][q] = psi[s * N + own_idx<N, E, SC::RF>(t, q)];
-    fft_forward<SC, 1>(v, lds, lay, tw, t);
+    for (int q = 0; q < E; ++q) {
+      const int k = own_idx<N, E, SC::RL>(t, q);
+      const double kk = (double)(k < N / 2 ? k : k - N);
+      const double re = (double)v[s][q].re, im = (double)v[s][q].im;
+      a = fma(kk * kk, fma(re, re, im * im), a);
+    }
+  }
+  acc[S + 1] = ck * a;
+  workgroup_sum<SC::TPC, S + 2>(acc, reinterpret_cast<double*>(smem_raw));
+  if (t == 0) {
 #pragma unroll
-    for (int q = 0; q < E; ++q) psi[s * N + own_idx<N, E, SC::RL>(t, q)] = v[0][q];
+    for (int k = 0; k < S + 2; ++k) out[k] = acc[k];
   }
 }
 
 constexpr size_t kMaxLds = 160 * 1024;
+
+// Dynamic LDS past 64 KB has to be allowed per kernel.
+hipError_t set_lds(const void* k, size_t bytes) {
+  if (bytes <= 64 * 1024) return hipSuccess;
+  return hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+}
 
 template <typename T, class SC, int S>
 hipError_t launch_prop(const DevView& d, void* psi, int64_t nsteps, int conj, int count) {
@@ -61,24 +104,21 @@ hipError_t launch_prop(const DevView& d, void* psi, int64_t nsteps, int conj, in
   if constexpr (SC::N == w4::N && S == 2) {
     constexpr size_t bytes = w4::lds_bytes<T>();
     auto k = k1d_w4_kernel<T>;
-    hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)bytes);
+    const hipError_t e = set_lds((const void*)k, bytes);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k, dim3(count), dim3(w4::kThreads), bytes, d.stream, (cx<T>*)psi,
                        (const cx<T>*)d.vexp, (const cx<T>*)d.kin, (const cx<T>*)d.tw[0], d.prog,
                        d.nact, nsteps, conj);
   } else if (one * S <= kMaxLds) {
     auto k = k1d_prop_kernel<T, SC, S, S>;
-    hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)(one * S));
+    const hipError_t e = set_lds((const void*)k, one * S);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k, dim3(count), dim3(SC::TPC), one * S, d.stream, (cx<T>*)psi,
                        (const cx<T>*)d.vexp, (const cx<T>*)d.kin, (const cx<T>*)d.tw[0], d.prog,
                        d.nact, nsteps, conj);
   } else {
     auto k = k1d_prop_kernel<T, SC, S, 1>;
-    hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)one);
+    const hipError_t e = set_lds((const void*)k, one);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k, dim3(count), dim3(SC::TPC), one, d.stream, (cx<T>*)psi,
                        (const cx<T>*)d.vexp, (const cx<T>*)d.kin, (const cx<T>*)d.tw[0], d.prog,
@@ -88,14 +128,14 @@ hipError_t launch_prop(const DevView& d, void* psi, int64_t nsteps, int conj, in
 }
 
 template <typename T, class SC, int S>
-hipError_t launch_fft(const DevView& d, void* psi) {
+hipError_t launch_obs(const DevView& d, const void* psi, const double* vraw, double ck,
+                      double* out) {
   constexpr size_t one = (size_t)lds_pencil<SC>() * sizeof(cx<T>);
-  auto k = k1d_fft_kernel<T, SC, S>;
-  hipError_t e =
-      hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)one);
+  auto k = k1d_obs_kernel<T, SC, S>;
+  const hipError_t e = set_lds((const void*)k, one);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k, dim3(1), dim3(SC::TPC), one, d.stream, (cx<T>*)psi,
-                     (const cx<T>*)d.tw[0]);
+  hipLaunchKernelGGL(k, dim3(1), dim3(SC::TPC), one, d.stream, (const cx<T>*)psi, vraw,
+                     (const cx<T>*)d.tw[0], ck, out);
   return hipGetLastError();
 }
 
@@ -148,10 +188,10 @@ hipError_t k1d_propagate(const DevView& d, void* psi, int64_t nsteps, int conj, 
   });
 }
 
-hipError_t k1d_fft_forward(const DevView& d, void* psi) {
-  if (d.timer) d.timer->break_chain();  // untimed work may precede this call
+hipError_t k1d_observe(const DevView& d, const void* psi, const double* vraw, double ck,
+                       double* out) {
   return dispatch(d.n[0], d.S, d.f64, [&]<typename T, class SC, int S>() {
-    return launch_fft<T, SC, S>(d, psi);
+    return launch_obs<T, SC, S>(d, psi, vraw, ck, out);
   });
 }
 

@@ -20,6 +20,7 @@
 #include <vector>
 
 #include "passes_3d.hpp"
+#include "reduce.hpp"
 
 namespace sop {
 namespace {
@@ -282,28 +283,28 @@ __global__ void __launch_bounds__(C * SC::TPC) __attribute__((amdgpu_waves_per_e
 
 // ---------------------------------------------------------------- y-pass
 // grid (N / C, N, surfaces x states): blockIdx.z picks one surface pencil set;
-// fy = the y factor of the kinetic set (AX_KIN)
-template <typename T, class SC, int C, int AX>
+// fy = the y factor of the kinetic set
+template <typename T, class SC, int C>
 __global__ void __launch_bounds__(C * SC::TPC)
     k3d_ypass(cx<T>* __restrict__ psi, const cx<T>* __restrict__ tw,
               const cx<T>* __restrict__ fy, int conj, const cx<T>* src) {
   extern __shared__ char smem_raw[];
   cx<T>* lds = reinterpret_cast<cx<T>*>(smem_raw);
   constexpr int64_t npts = (int64_t)SC::N * SC::N * SC::N;
-  ypass_body<T, SC, C, AX>(psi + blockIdx.z * npts, tw, fy, conj, lds, blockIdx.x, blockIdx.y,
+  ypass_body<T, SC, C>(psi + blockIdx.z * npts, tw, fy, conj, lds, blockIdx.x, blockIdx.y,
                            (int)threadIdx.x, src ? src + blockIdx.z * npts : nullptr);
 }
 
 // ---------------------------------------------------------------- x-pass
-// grid (N / ROWS, N, surfaces x states); fx = the x factor (AX_KIN)
-template <typename T, class SC, int ROWS, int AX>
+// grid (N / ROWS, N, surfaces x states); fx = the x factor
+template <typename T, class SC, int ROWS>
 __global__ void __launch_bounds__(ROWS * SC::TPC)
     k3d_xpass(cx<T>* __restrict__ psi, const cx<T>* __restrict__ tw,
               const cx<T>* __restrict__ fx, int conj, const cx<T>* src) {
   extern __shared__ char smem_raw[];
   cx<T>* lds = reinterpret_cast<cx<T>*>(smem_raw);
   constexpr int64_t npts = (int64_t)SC::N * SC::N * SC::N;
-  xpass_body<T, SC, ROWS, AX>(psi + blockIdx.z * npts, tw, fx, conj, lds, blockIdx.x, blockIdx.y,
+  xpass_body<T, SC, ROWS>(psi + blockIdx.z * npts, tw, fx, conj, lds, blockIdx.x, blockIdx.y,
                               (int)threadIdx.x, src ? src + blockIdx.z * npts : nullptr);
 }
 
@@ -317,6 +318,151 @@ __global__ void __launch_bounds__(SC::N * SC::TPC)
   cx<T>* lds = reinterpret_cast<cx<T>*>(smem_raw);
   constexpr int64_t npts = (int64_t)SC::N * SC::N * SC::N;
   plane_body<T, SC>(psi + blockIdx.y * npts, tw, kin, conj, lds, blockIdx.x);
+}
+
+// ---------------------------------------------------------------- observables
+// T is a sum over the axes, so <T> = sum_d (1/n_d) sum T_d(k) |F_d psi|^2 with
+// the transform along axis d alone (Parseval): three passes that read psi and
+// write only their partial sums, where the full transform of a copy moves the
+// state nine times.  The z-pass, which holds every surface of its points,
+// also sums |psi_s|^2 and psi^dag V psi.  Bound by the reads: 128^3 x 3 FP64
+// 190 us as a copy, three transform passes and two reductions, 83 us so
+// (three state reads and the V-table).
+
+// sum over the owned frequencies of k^2 |v|^2 (k signed, FP64)
+template <typename T, class SC>
+__device__ __forceinline__ double k2_sum(const cx<T> (&v)[SC::E], int t) {
+  constexpr int N = SC::N, E = SC::E;
+  double a = 0.0;
+#pragma unroll
+  for (int q = 0; q < E; ++q) {
+    const int k = own_idx<N, E, SC::RL>(t, q);
+    const double kk = (double)(k < N / 2 ? k : k - N);
+    const double re = (double)v[q].re, im = (double)v[q].im;
+    a = fma(kk * kk, fma(re, re, im * im), a);
+  }
+  return a;
+}
+
+// grid (N / C, N): partial row (S + 2 values) of block (bx, by)
+template <typename T, class SC, int S, int C>
+__global__ void __launch_bounds__(C * SC::TPC)
+    k3d_obs_z(const cx<T>* __restrict__ psi, const double* __restrict__ vraw,
+              const cx<T>* __restrict__ tw, double ck, double* __restrict__ part) {
+  extern __shared__ char smem_raw[];
+  cx<T>* lds = reinterpret_cast<cx<T>*>(smem_raw);
+  constexpr int N = SC::N, E = SC::E;
+  constexpr uint32_t plane = (uint32_t)N * N;
+  constexpr int64_t npts = (int64_t)plane * N;
+  const int col = threadIdx.x % C, t = threadIdx.x / C;
+  const uint32_t off0 = (uint32_t)blockIdx.y * N + blockIdx.x * C + col;
+  cx<T> v[S][E];
+#pragma unroll
+  for (int s = 0; s < S; ++s) {
+    const auto rs = rsrc(psi + s * npts, (uint32_t)npts);
+#pragma unroll
+    for (int q = 0; q < E; ++q) v[s][q] = ld<T>(rs, own_idx<N, E, SC::RF>(t, q) * plane + off0);
+  }
+  double acc[S + 2];
+#pragma unroll
+  for (int k = 0; k < S + 2; ++k) acc[k] = 0.0;
+#pragma unroll
+  for (int q = 0; q < E; ++q) {
+    const int64_t x = (int64_t)own_idx<N, E, SC::RF>(t, q) * plane + off0;
+    int e = 0;
+#pragma unroll
+    for (int i = 0; i < S; ++i)
+#pragma unroll
+      for (int j = i; j < S; ++j) {
+        // Re(conj(psi_i) psi_j), counted twice off the diagonal
+        const double rr = (double)v[i][q].re * (double)v[j][q].re +
+                          (double)v[i][q].im * (double)v[j][q].im;
+        if (i == j) acc[i] += rr;
+        acc[S] += (i == j ? 1.0 : 2.0) * vraw[(int64_t)e * npts + x] * rr;
+        ++e;
+      }
+  }
+  const LayStrided lay{col, 0, C};
+#pragma unroll
+  for (int s = 0; s < S; ++s) {
+    fft_forward<SC, 1>(v + s, lds, lay, tw, t);
+    acc[S + 1] += k2_sum<T, SC>(v[s], t);
+  }
+  acc[S + 1] *= ck;
+  workgroup_sum<C * SC::TPC, S + 2>(acc, reinterpret_cast<double*>(smem_raw));
+  if (threadIdx.x == 0) {
+    double* o = part + ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * (S + 2);
+#pragma unroll
+    for (int k = 0; k < S + 2; ++k) o[k] = acc[k];
+  }
+}
+
+// grid (N / C, N, S): one partial value a block
+template <typename T, class SC, int C>
+__global__ void __launch_bounds__(C * SC::TPC)
+    k3d_obs_y(const cx<T>* __restrict__ psi, const cx<T>* __restrict__ tw, double ck,
+              double* __restrict__ part) {
+  extern __shared__ char smem_raw[];
+  cx<T>* lds = reinterpret_cast<cx<T>*>(smem_raw);
+  constexpr int N = SC::N, E = SC::E;
+  constexpr int64_t plane = (int64_t)N * N;
+  const int col = threadIdx.x % C, t = threadIdx.x / C;
+  const auto in = rsrc(psi + (blockIdx.z * (int64_t)N + blockIdx.y) * plane, (uint32_t)plane);
+  cx<T>* const tws = lds + C * N;
+  stage_blocks<T, N, 1>(tws, {tw}, threadIdx.x, C * SC::TPC);
+  cx<T> v[1][E];
+#pragma unroll
+  for (int q = 0; q < E; ++q)
+    v[0][q] = ld<T>(in, own_idx<N, E, SC::RF>(t, q) * N + blockIdx.x * C + col);
+  fft_forward<SC, 1>(v, lds, LayStrided{col, 0, C}, tws, t);
+  double acc[1] = {ck * k2_sum<T, SC>(v[0], t)};
+  workgroup_sum<C * SC::TPC, 1>(acc, reinterpret_cast<double*>(smem_raw));
+  if (threadIdx.x == 0)
+    part[((size_t)blockIdx.z * N + blockIdx.y) * gridDim.x + blockIdx.x] = acc[0];
+}
+
+// grid (N / ROWS, N, S): one partial value a block
+template <typename T, class SC, int ROWS>
+__global__ void __launch_bounds__(ROWS * SC::TPC)
+    k3d_obs_x(const cx<T>* __restrict__ psi, const cx<T>* __restrict__ tw, double ck,
+              double* __restrict__ part) {
+  extern __shared__ char smem_raw[];
+  cx<T>* lds = reinterpret_cast<cx<T>*>(smem_raw);
+  constexpr int N = SC::N, E = SC::E, TPC = SC::TPC;
+  constexpr int64_t plane = (int64_t)N * N;
+  const int t = threadIdx.x % TPC, row = threadIdx.x / TPC;
+  const auto in = rsrc(psi + (blockIdx.z * (int64_t)N + blockIdx.y) * plane, (uint32_t)plane);
+  cx<T>* const tws = lds + ROWS * (N + N / 16);
+  stage_blocks<T, N, 1>(tws, {tw}, threadIdx.x, ROWS * TPC);
+  cx<T> v[1][E];
+#pragma unroll
+  for (int q = 0; q < E; ++q)
+    v[0][q] = ld<T>(in, own_idx<N, E, SC::RF>(t, q) + (blockIdx.x * ROWS + row) * N);
+  fft_forward<SC, 1>(v, lds, LayPadded{row * (N + N / 16), 0}, tws, t);
+  double acc[1] = {ck * k2_sum<T, SC>(v[0], t)};
+  workgroup_sum<ROWS * TPC, 1>(acc, reinterpret_cast<double*>(smem_raw));
+  if (threadIdx.x == 0)
+    part[((size_t)blockIdx.z * N + blockIdx.y) * gridDim.x + blockIdx.x] = acc[0];
+}
+
+// Block v < S + 1: column v of the nz rows of S + 2 values; block S + 1: the
+// kinetic column and the nk values after the rows.
+constexpr int kObsFinal = 1024;
+template <int S>
+__global__ void __launch_bounds__(kObsFinal)
+    k3d_obs_final(const double* __restrict__ part, int nz, int nk, double* __restrict__ out) {
+  __shared__ double red[kObsFinal / 64];
+  const int v = blockIdx.x;
+  double a[1] = {0.0};
+#pragma unroll 4
+  for (int i = threadIdx.x; i < nz; i += kObsFinal) a[0] += part[(size_t)i * (S + 2) + v];
+  if (v == S + 1) {
+    const double* const k = part + (size_t)nz * (S + 2);
+#pragma unroll 4
+    for (int i = threadIdx.x; i < nk; i += kObsFinal) a[0] += k[i];
+  }
+  workgroup_sum<kObsFinal, 1>(a, red);
+  if (threadIdx.x == 0) out[v] = a[0];
 }
 
 // ---------------------------------------------------------------- launchers
@@ -431,30 +577,28 @@ struct Passes {
                        AX == AX_KIN ? kfac(d, tidx, 0) : nullptr, d.vtaus, src);
     return hipGetLastError();
   }
-  template <int AX>
   static hipError_t ypass(const DevView& d, cx<T>* psi, int tidx, int conj,
                           const cx<T>* src = nullptr) {
-    auto k = k3d_ypass<T, XS, C, AX>;
+    auto k = k3d_ypass<T, XS, C>;
     const size_t lds = y_lds_elems<T, N>(C) * sizeof(cx<T>);
     hipError_t e = set_lds(k, lds);
     if (e != hipSuccess) return e;
     TimedLaunch tl(d, KIND_YPASS, pass_bytes(d, 0));
     hipLaunchKernelGGL(k, dim3(N / C, N, d.S * d.count), dim3(C * XS::TPC), lds, d.stream, psi,
-                       (const cx<T>*)d.tw[1], AX == AX_KIN ? kfac(d, tidx, 1) : nullptr, conj,
+                       (const cx<T>*)d.tw[1], kfac(d, tidx, 1), conj,
                        src);
     return hipGetLastError();
   }
-  template <int AX>
   static hipError_t xpass(const DevView& d, cx<T>* psi, int tidx, int conj,
                           const cx<T>* src = nullptr) {
-    auto k = k3d_xpass<T, XS, ROWS, AX>;
+    auto k = k3d_xpass<T, XS, ROWS>;
     const size_t lds = x_lds_elems<T, N>(ROWS) * sizeof(cx<T>);
     hipError_t e = set_lds(k, lds);
     if (e != hipSuccess) return e;
     TimedLaunch tl(d, KIND_XPASS, pass_bytes(d, 0));
     hipLaunchKernelGGL(k, dim3(N / ROWS, N, d.S * d.count), dim3(ROWS * XS::TPC), lds,
                        d.stream, psi, (const cx<T>*)d.tw[2],
-                       AX == AX_KIN ? kfac(d, tidx, 2) : nullptr, conj, src);
+                       kfac(d, tidx, 2), conj, src);
     return hipGetLastError();
   }
 
@@ -480,8 +624,8 @@ struct Passes {
       case PassDesc::Z:
         return p.kz ? z<AX_KIN>(d, psi, p.nv, p.iv0, p.iv1, p.tidx, conj)
                     : z<AX_NONE>(d, psi, p.nv, p.iv0, p.iv1, 0, conj);
-      case PassDesc::Y: return ypass<AX_KIN>(d, psi, p.tidx, conj);
-      case PassDesc::X: return xpass<AX_KIN>(d, psi, p.tidx, conj);
+      case PassDesc::Y: return ypass(d, psi, p.tidx, conj);
+      case PassDesc::X: return xpass(d, psi, p.tidx, conj);
       default: return plane(d, psi, p.tidx, conj);
     }
   }
@@ -564,14 +708,43 @@ struct Passes {
     return g3 ? hipGraphLaunch(g3, d.stream) : hipSuccess;
   }
 
-  // Forward transform of every surface (momentum representation, natural
-  // order, unnormalised) for the observables.
-  static hipError_t fft_forward(const DevView& d, void* vpsi) {
-    cx<T>* psi = (cx<T>*)vpsi;
-    hipError_t e = z<AX_FWD>(d, psi, 0, 0, 0, 0, 0);
-    if (e != hipSuccess) return e;
-    if ((e = ypass<AX_FWD>(d, psi, 0, 0)) != hipSuccess) return e;
-    return xpass<AX_FWD>(d, psi, 0, 0);
+  // Rows of partial sums of an observables call: kz from the z-pass (S + 2
+  // values each), ky and kx from the y- and x-passes (one value each).
+  static constexpr int kObsZ = N / CZ * N, kObsY = N / C * N * S, kObsX = N / ROWS * N * S;
+
+  // sum |psi_s|^2, sum psi^dag V psi and the kinetic sum (weights c[axis] k^2)
+  // into out[S + 2], by way of `part`.
+  static hipError_t observe(const DevView& d, const cx<T>* psi, const double* vraw,
+                            const double* c, double* part, double* out) {
+    double* const py = part + (size_t)kObsZ * (S + 2);
+    double* const px = py + kObsY;
+    {
+      auto k = k3d_obs_z<T, SC, S, CZ>;
+      const size_t lds = (size_t)CZ * N * sizeof(cx<T>);
+      const hipError_t e = set_lds(k, lds);
+      if (e != hipSuccess) return e;
+      hipLaunchKernelGGL(k, dim3(N / CZ, N), dim3(CZ * SC::TPC), lds, d.stream, psi, vraw,
+                         (const cx<T>*)d.tw[0], c[0], part);
+    }
+    {
+      auto k = k3d_obs_y<T, XS, C>;
+      const size_t lds = y_lds_elems<T, N>(C) * sizeof(cx<T>);
+      const hipError_t e = set_lds(k, lds);
+      if (e != hipSuccess) return e;
+      hipLaunchKernelGGL(k, dim3(N / C, N, S), dim3(C * XS::TPC), lds, d.stream, psi,
+                         (const cx<T>*)d.tw[1], c[1], py);
+    }
+    {
+      auto k = k3d_obs_x<T, XS, ROWS>;
+      const size_t lds = x_lds_elems<T, N>(ROWS) * sizeof(cx<T>);
+      const hipError_t e = set_lds(k, lds);
+      if (e != hipSuccess) return e;
+      hipLaunchKernelGGL(k, dim3(N / ROWS, N, S), dim3(ROWS * XS::TPC), lds, d.stream, psi,
+                         (const cx<T>*)d.tw[2], c[2], px);
+    }
+    hipLaunchKernelGGL((k3d_obs_final<S>), dim3(S + 2), dim3(kObsFinal), 0, d.stream, part,
+                       kObsZ, kObsY + kObsX, out);
+    return hipGetLastError();
   }
 
   // ------------------------------------------------------------ adjoint
@@ -630,8 +803,8 @@ struct Passes {
               r = p.kz ? za<true>(d, a, p.nv, p.iv0, p.iv1, p.tidx)
                        : za<false>(d, a, p.nv, p.iv0, p.iv1, 0);
               break;
-            case PassDesc::Y: r = ypass<AX_KIN>(d2, stk, p.tidx, 1); break;
-            default: r = xpass<AX_KIN>(d2, stk, p.tidx, 1); break;
+            case PassDesc::Y: r = ypass(d2, stk, p.tidx, 1); break;
+            default: r = xpass(d2, stk, p.tidx, 1); break;
           }
           if (r != hipSuccess) return r;
         }
@@ -722,8 +895,8 @@ hipError_t k3d_axis_kinetic(const DevView& d, void* psi, int axis, const void* s
     const cx<T>* u = (const cx<T>*)src;
     switch (axis) {
       case 0: return P::template z<AX_KIN>(d, v, 0, 0, 0, 0, 0, u);
-      case 1: return P::template ypass<AX_KIN>(d, v, 0, 0, u);
-      case 2: return P::template xpass<AX_KIN>(d, v, 0, 0, u);
+      case 1: return P::ypass(d, v, 0, 0, u);
+      case 2: return P::xpass(d, v, 0, 0, u);
       default: return hipErrorInvalidValue;
     }
   });
@@ -771,10 +944,20 @@ hipError_t k3d_adjoint_backward(const DevView& d, const AdjointView& a, int64_t 
   }
 }
 
-hipError_t k3d_fft_forward(const DevView& d, void* psi) {
-  if (d.timer) d.timer->break_chain();  // untimed work may precede this call
+size_t k3d_obs_partials(int n, int S, bool f64) {
+  size_t r = 0;
+  (void)dispatch(n, S, f64, [&]<typename T, class SC, int S_>() -> hipError_t {
+    using P = Passes<T, SC, S_>;
+    r = (size_t)P::kObsZ * (S_ + 2) + P::kObsY + P::kObsX;
+    return hipSuccess;
+  });
+  return r;
+}
+
+hipError_t k3d_observe(const DevView& d, const void* psi, const double* vraw, const double* c,
+                       double* part, double* out) {
   return dispatch(d.n[0], d.S, d.f64, [&]<typename T, class SC, int S>() {
-    return Passes<T, SC, S>::fft_forward(d, psi);
+    return Passes<T, SC, S>::observe(d, (const cx<T>*)psi, vraw, c, part, out);
   });
 }
 

@@ -11,8 +11,9 @@
 // triangle is stored structure-of-arrays, [unique][entry][point] for 1D
 // grids, or tile-contiguous for the 3D z-pass ([unique][tile][z][entry][col]).
 //
-// Reductions: norm, surface populations and <V> from psi, <T> from its
-// forward transform, and <psi|phi>; every sum is FP64 with a fixed block
+// Reductions: surface populations and <V> from psi, <psi|phi> and distances
+// (the observables' sums with <T> are in kernels_1d.hip and kernels_3d.hip,
+// with the transforms they need); every sum is FP64 with a fixed block
 // count and a fixed-order tree, so results are bitwise reproducible.
 #include "fft_core.hpp"
 #include "internal.hpp"
@@ -239,36 +240,6 @@ __global__ void __launch_bounds__(kReduceThreads)
     acc[S] += ev;
   }
   block_sum<S + 1>(acc, partials + (size_t)blockIdx.x * (S + 1));
-}
-
-// Per block: sum_k T(k) sum_s |psi_hat_s(k)|^2 with T(k) = sum_d inv_mass_d
-// (hbar kappa_d)^2 / 2, kappa_d = 2 pi k'_d / (n_d dx_d).
-template <typename T>
-__global__ void __launch_bounds__(kReduceThreads)
-    k_obs_kinetic(const cx<T>* __restrict__ ph, int S, int ndim, int n0, int n1, int n2,
-                  double c0, double c1, double c2, double* __restrict__ partials) {
-  const int64_t npts = (int64_t)n0 * n1 * n2;
-  double acc[1] = {0.0};
-  for (int64_t x = (int64_t)blockIdx.x * kReduceThreads + threadIdx.x; x < npts;
-       x += (int64_t)gridDim.x * kReduceThreads) {
-    const int k2 = (int)(x % n2);
-    const int k1 = (int)((x / n2) % n1);
-    const int k0 = (int)(x / ((int64_t)n1 * n2));
-    auto sq = [](int k, int n) {
-      const double kk = (k < n / 2) ? (double)k : (double)(k - n);
-      return kk * kk;
-    };
-    // c_d = inv_mass_d * (hbar * 2 pi / (n_d dx_d))^2 / 2
-    double t = c0 * sq(k0, n0);
-    if (ndim > 1) t += c1 * sq(k1, n1) + c2 * sq(k2, n2);
-    double m = 0.0;
-    for (int s = 0; s < S; ++s) {
-      const cx<T> p = ph[s * npts + x];
-      m += (double)p.re * (double)p.re + (double)p.im * (double)p.im;
-    }
-    acc[0] += t * m;
-  }
-  block_sum<1>(acc, partials + blockIdx.x);
 }
 
 template <typename T>
@@ -518,48 +489,6 @@ hipError_t form_eigq(const DevView& d, const double* vraw_dev, int tile, void* o
     case 3: hipLaunchKernelGGL(k_form_eigq<3>, dim3(blocks), dim3(256), 0, d.stream, vraw_dev, d.npts, tile, d.n[0], o, dtab, dmask, s_dev); break;
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
-}
-
-// partials layout: [kReduceBlocks][S+1] for the pointwise sums, then
-// [kReduceBlocks] for the kinetic sum.  out_dev receives S + 2 raw sums:
-// sum |psi_s|^2 (S values), sum psi^dag V psi, sum T |psi_hat|^2.
-hipError_t obs_reduce(const DevView& d, const void* psi, const void* psi_hat,
-                      const double* vraw_dev, const double* inv_mass, const double* dx,
-                      double hbar, double* partials, double* out_dev) {
-  hipError_t e;
-  switch (d.S) {
-    case 1: e = d.f64 ? obs_points_impl<1, double>(d, psi, vraw_dev, partials)
-                      : obs_points_impl<1, float>(d, psi, vraw_dev, partials); break;
-    case 2: e = d.f64 ? obs_points_impl<2, double>(d, psi, vraw_dev, partials)
-                      : obs_points_impl<2, float>(d, psi, vraw_dev, partials); break;
-    case 3: e = d.f64 ? obs_points_impl<3, double>(d, psi, vraw_dev, partials)
-                      : obs_points_impl<3, float>(d, psi, vraw_dev, partials); break;
-    default: return hipErrorInvalidValue;
-  }
-  if (e != hipSuccess) return e;
-  const int nv = d.S + 1;
-  double* kpart = partials + (size_t)kReduceBlocks * nv;
-  double c[3] = {0, 0, 0};
-  const double twopi = 6.283185307179586476925286766559;
-  for (int a = 0; a < d.ndim; ++a) {
-    const double kap = hbar * twopi / ((double)d.n[a] * dx[a]);
-    c[a] = 0.5 * inv_mass[a] * kap * kap;
-  }
-  if (d.f64)
-    hipLaunchKernelGGL(k_obs_kinetic<double>, dim3(kReduceBlocks), dim3(kReduceThreads), 0,
-                       d.stream, (const cx<double>*)psi_hat, d.S, d.ndim, d.n[0], d.n[1], d.n[2],
-                       c[0], c[1], c[2], kpart);
-  else
-    hipLaunchKernelGGL(k_obs_kinetic<float>, dim3(kReduceBlocks), dim3(kReduceThreads), 0,
-                       d.stream, (const cx<float>*)psi_hat, d.S, d.ndim, d.n[0], d.n[1], d.n[2],
-                       c[0], c[1], c[2], kpart);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(k_final, dim3(1), dim3(kReduceThreads), 0, d.stream, partials,
-                     kReduceBlocks, nv, out_dev);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(k_final, dim3(1), dim3(kReduceThreads), 0, d.stream, kpart, kReduceBlocks,
-                     1, out_dev + nv);
   return hipGetLastError();
 }
 

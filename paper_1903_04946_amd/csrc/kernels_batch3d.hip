@@ -74,7 +74,7 @@ __global__ void __launch_bounds__(C * SC::TPC)
   if (c >= m.cycles) return;
   constexpr int64_t npts = (int64_t)SC::N * SC::N * SC::N;
   const cx<T>* tw = (const cx<T>*)m.tw + SC::N * Split<T>::rep;  // the y block
-  ypass_body<T, SC, C, AX_KIN>((cx<T>*)m.psi + s * npts, tw, cycle_kin<T>(m, c, 1), m.conj, lds,
+  ypass_body<T, SC, C>((cx<T>*)m.psi + s * npts, tw, cycle_kin<T>(m, c, 1), m.conj, lds,
                                blockIdx.x, blockIdx.y);
 }
 
@@ -89,7 +89,7 @@ __global__ void __launch_bounds__(ROWS * SC::TPC)
   if (c >= m.cycles) return;
   constexpr int64_t npts = (int64_t)SC::N * SC::N * SC::N;
   const cx<T>* tw = (const cx<T>*)m.tw + 2 * SC::N * Split<T>::rep;  // the x block
-  xpass_body<T, SC, ROWS, AX_KIN>((cx<T>*)m.psi + s * npts, tw, cycle_kin<T>(m, c, 2), m.conj,
+  xpass_body<T, SC, ROWS>((cx<T>*)m.psi + s * npts, tw, cycle_kin<T>(m, c, 2), m.conj,
                                   lds, blockIdx.x, blockIdx.y);
 }
 
@@ -272,10 +272,10 @@ __global__ void __launch_bounds__(kQThreads)
       const int s = tile / TZ, rem = tile % TZ;
       const int bx = rem % NB, z = rem / NB;
       if (r.kind == B3_Y)
-        ypass_body<T, SC, W, AX_KIN>(psi + s * npts, tw + A, cycle_kin<T>(m, c, 1), m.conj, lds,
+        ypass_body<T, SC, W>(psi + s * npts, tw + A, cycle_kin<T>(m, c, 1), m.conj, lds,
                                      bx, z, ln);
       else
-        xpass_body<T, SC, W, AX_KIN>(psi + s * npts, tw + 2 * A, cycle_kin<T>(m, c, 2), m.conj,
+        xpass_body<T, SC, W>(psi + s * npts, tw + 2 * A, cycle_kin<T>(m, c, 2), m.conj,
                                      lds, bx, z, ln);
     }
     // every wave's stores are visible device-wide before the counter moves

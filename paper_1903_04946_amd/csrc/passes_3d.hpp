@@ -114,10 +114,8 @@ __device__ __forceinline__ void stage_blocks(cx<T>* dst, const cx<T>* const (&sr
 
 // What a pass does along its axis after its pointwise work:
 //   AX_NONE: nothing (z-pass carrying only potential actions);
-//   AX_KIN : forward FFT -> per-axis kinetic factor -> inverse FFT;
-//   AX_FWD : forward FFT only, output in the momentum representation (the
-//            observables' transform).
-enum { AX_NONE = 0, AX_KIN = 1, AX_FWD = 2 };
+//   AX_KIN : forward FFT -> per-axis kinetic factor -> inverse FFT.
+enum { AX_NONE = 0, AX_KIN = 1 };
 
 // v (forward-transformed, radix-RL ownership) *= f[k] (conjugated factor
 // when conj): the kinetic factor of one axis (a split block in FP32).
@@ -280,28 +278,25 @@ __device__ __forceinline__ void zpass_body(cx<T>* __restrict__ psi,
     if (nv >= 1) vact(iv0);
     if (nv >= 2) vact(iv1);
   }
-  if constexpr (AX != AX_NONE) {
+  if constexpr (AX == AX_KIN) {
 #pragma unroll
     for (int s = 0; s < S; ++s) fft_forward<SC, 1>(v + s, lds, lay, tw, t);
-  }
-  if constexpr (AX == AX_KIN) {
     axis_phase<T, SC, S>(v, fz, csign, t);
 #pragma unroll
     for (int s = 0; s < S; ++s) fft_inverse<SC, 1>(v + s, lds, lay, tw, t);
   }
-  constexpr int ROUT = AX == AX_FWD ? SC::RL : SC::RF;
 #pragma unroll
   for (int s = 0; s < S; ++s) {
     const auto rs = rsrc(psi + s * npts, (uint32_t)npts);
 #pragma unroll
-    for (int q = 0; q < E; ++q) st(rs, own_idx<N, E, ROUT>(t, q) * plane + off0, v[s][q]);
+    for (int q = 0; q < E; ++q) st(rs, own_idx<N, E, SC::RF>(t, q) * plane + off0, v[s][q]);
   }
 }
 
 // ---------------------------------------------------------------- y-pass
 // One surface `psi_s` [N^3]; block (bx, z) owns columns bx*C .. bx*C+C-1 of
-// plane z.  AX = AX_KIN (factor fy) or AX_FWD.
-template <typename T, class SC, int C, int AX>
+// plane z; fy = the y factor.
+template <typename T, class SC, int C>
 __device__ __forceinline__ void ypass_body(cx<T>* __restrict__ psi_s,
                                            const cx<T>* __restrict__ tw,
                                            const cx<T>* __restrict__ fy, int conj, cx<T>* lds,
@@ -315,28 +310,21 @@ __device__ __forceinline__ void ypass_body(cx<T>* __restrict__ psi_s,
   const auto bin = rsrc((src_s ? src_s : psi_s) + z * plane, (uint32_t)plane);
   const LayStrided lay{col, 0, C};
   cx<T>* const tws = lds + C * N;  // staged twiddles and y factor
-  if constexpr (AX == AX_KIN) {
-    stage_blocks<T, N, 2>(tws, {tw, fy}, lane, C * SC::TPC);
-  } else {
-    stage_blocks<T, N, 1>(tws, {tw}, lane, C * SC::TPC);
-  }
+  stage_blocks<T, N, 2>(tws, {tw, fy}, lane, C * SC::TPC);
   cx<T> v[1][E];
 #pragma unroll
   for (int q = 0; q < E; ++q) v[0][q] = ld<T>(bin, own_idx<N, E, SC::RF>(t, q) * N + x);
   fft_forward<SC, 1>(v, lds, lay, tws, t);
-  if constexpr (AX == AX_KIN) {
-    axis_phase<T, SC, 1>(v, tws + axis_block<T, N>(), conj ? (T)-1 : (T)1, t);
-    fft_inverse<SC, 1>(v, lds, lay, tws, t);
-  }
-  constexpr int ROUT = AX == AX_FWD ? SC::RL : SC::RF;
+  axis_phase<T, SC, 1>(v, tws + axis_block<T, N>(), conj ? (T)-1 : (T)1, t);
+  fft_inverse<SC, 1>(v, lds, lay, tws, t);
 #pragma unroll
-  for (int q = 0; q < E; ++q) st(base, own_idx<N, E, ROUT>(t, q) * N + x, v[0][q]);
+  for (int q = 0; q < E; ++q) st(base, own_idx<N, E, SC::RF>(t, q) * N + x, v[0][q]);
 }
 
 // ---------------------------------------------------------------- x-pass
 // One surface `psi_s`; block (bx, z) owns rows bx*ROWS .. bx*ROWS+ROWS-1 of
-// plane z.  AX = AX_KIN (factor fx) or AX_FWD.
-template <typename T, class SC, int ROWS, int AX>
+// plane z; fx = the x factor.
+template <typename T, class SC, int ROWS>
 __device__ __forceinline__ void xpass_body(cx<T>* __restrict__ psi_s,
                                            const cx<T>* __restrict__ tw,
                                            const cx<T>* __restrict__ fx, int conj, cx<T>* lds,
@@ -351,22 +339,15 @@ __device__ __forceinline__ void xpass_body(cx<T>* __restrict__ psi_s,
   const uint32_t yo = (uint32_t)y * N;
   const LayPadded lay{row * (N + N / 16), 0};
   cx<T>* const tws = lds + ROWS * (N + N / 16);  // staged twiddles and x factor
-  if constexpr (AX == AX_KIN) {
-    stage_blocks<T, N, 2>(tws, {tw, fx}, lane, ROWS * TPC);
-  } else {
-    stage_blocks<T, N, 1>(tws, {tw}, lane, ROWS * TPC);
-  }
+  stage_blocks<T, N, 2>(tws, {tw, fx}, lane, ROWS * TPC);
   cx<T> v[1][E];
 #pragma unroll
   for (int q = 0; q < E; ++q) v[0][q] = ld<T>(bin, own_idx<N, E, SC::RF>(t, q) + yo);
   fft_forward<SC, 1>(v, lds, lay, tws, t);
-  if constexpr (AX == AX_KIN) {
-    axis_phase<T, SC, 1>(v, tws + axis_block<T, N>(), conj ? (T)-1 : (T)1, t);
-    fft_inverse<SC, 1>(v, lds, lay, tws, t);
-  }
-  constexpr int ROUT = AX == AX_FWD ? SC::RL : SC::RF;
+  axis_phase<T, SC, 1>(v, tws + axis_block<T, N>(), conj ? (T)-1 : (T)1, t);
+  fft_inverse<SC, 1>(v, lds, lay, tws, t);
 #pragma unroll
-  for (int q = 0; q < E; ++q) st(base, own_idx<N, E, ROUT>(t, q) + yo, v[0][q]);
+  for (int q = 0; q < E; ++q) st(base, own_idx<N, E, SC::RF>(t, q) + yo, v[0][q]);
 }
 
 // ---------------------------------------------------------------- xy plane

@@ -222,6 +222,7 @@ struct sop_plan {
   std::vector<double> vtaus;  // c dt / hbar of the potential tables
   std::vector<double> ttaus;  // c dt of the kinetic factor sets
   DevView dv;
+  void* d_base = nullptr;  // the allocation that holds the buffers down to d_out
   double* d_vraw = nullptr;
   void* d_vexp = nullptr;
   void* d_kin = nullptr;
@@ -229,7 +230,6 @@ struct sop_plan {
   int* d_prog = nullptr;
   int* d_prog1 = nullptr;  // single-action programs {V(0), T(0)}
   double* d_taus = nullptr;
-  void* d_scratch = nullptr;
   void* d_trap = nullptr;  // trapezoidal rule: residual, stats, stage taus
   size_t trap_bytes = 0;
   void* d_iws = nullptr;  // sop_interpolate workspace (grown on demand)
@@ -240,6 +240,7 @@ struct sop_plan {
   void* d_akin = nullptr;
   double* d_part = nullptr;
   double* d_out = nullptr;
+  double* h_out = nullptr;  // pinned: the sums of an observables call (from the first one on)
   size_t table_bytes = 0;
   bool eig_form = false;  // d_vexp holds the compact eigen form (3D FP64, S >= 2)
   double vbound = 0;      // max over points of max_i sum_j |V_ij| (bounds |lam|)
@@ -300,9 +301,8 @@ hipError_t dalloc(sop_plan* p, T** ptr, size_t bytes) {
 
 void free_plan(sop_plan* p) {
   if (!p) return;
-  void* bufs[] = {p->d_vraw, p->d_vexp, p->d_kin, p->d_tw, p->d_prog, p->d_prog1, p->d_taus,
-                  p->d_scratch, p->d_atab, p->d_akin, p->d_part, p->d_out, p->d_vbase,
-                  p->d_dv, p->d_theta, p->d_eig, p->d_w, p->d_drive, p->d_iws, p->d_trap};
+  void* bufs[] = {p->d_base, p->d_atab, p->d_akin,  p->d_vbase, p->d_dv,  p->d_theta,
+                  p->d_eig,  p->d_w,    p->d_drive, p->d_iws,   p->d_trap};
   delete p->graphs;
   for (auto& kv : p->t3graphs) (void)hipGraphExecDestroy(kv.second);
   for (void* b : bufs) {
@@ -312,6 +312,7 @@ void free_plan(sop_plan* p) {
     else
       (void)hipFree(b);
   }
+  if (p->h_out) (void)hipHostFree(p->h_out);
   delete p->timer;
   delete p;
 }
@@ -456,11 +457,6 @@ sop_status validate(const sop_plan_desc* d) {
   if (d->nparams < 0 || d->nparams > sop::kMaxParams)
     return fail(SOP_ERR_INVALID, "nparams must be 0..8");
   if (d->nparams > 0 && !d->dvtables) return fail(SOP_ERR_INVALID, "dvtables required");
-  return SOP_OK;
-}
-
-sop_status ensure_scratch(sop_plan* p) {
-  if (!p->d_scratch) HIPTRY(dalloc(p, &p->d_scratch, (size_t)p->S * p->npts * p->csize));
   return SOP_OK;
 }
 
@@ -610,18 +606,36 @@ sop_status sop_plan_create_with_allocator(const sop_plan_desc* desc, void* hip_s
   const int nax = p->ndim == 1 ? 1 : 3;
   const size_t kbytes = tc.size() * nax * p->n[0] * p->csize * rep;
   const size_t wbytes = (size_t)nax * p->n[0] * p->csize * rep;
-  if (dalloc(p, &p->d_vraw, vbytes) != hipSuccess || dalloc(p, &p->d_vexp, tbytes) != hipSuccess ||
-      dalloc(p, &p->d_kin, kbytes) != hipSuccess || dalloc(p, &p->d_tw, wbytes) != hipSuccess ||
-      dalloc(p, &p->d_prog, prog.size() * sizeof(int)) != hipSuccess ||
-      dalloc(p, &p->d_prog1, 2 * sizeof(int)) != hipSuccess ||
-      dalloc(p, &p->d_taus, (vc.size() + 1) * sizeof(double)) != hipSuccess ||
-      dalloc(p, &p->d_part,
-             (size_t)sop::kReduceBlocks * (S + 2 + sop::kMaxParams) * sizeof(double)) !=
-          hipSuccess ||
-      dalloc(p, &p->d_out, 8 * sizeof(double)) != hipSuccess) {
+  // one allocation for the plan's tables and small buffers
+  const size_t parts = std::max((size_t)sop::kReduceBlocks * (S + 2 + sop::kMaxParams),
+                                p->ndim == 3 ? sop::k3d_obs_partials(p->n[0], S, f64) : 0);
+  size_t total = 0;
+  auto place = [&](size_t bytes) {
+    // tables of a megabyte and more start on a large page, as allocations of
+    // their own do
+    const size_t al = bytes >= ((size_t)1 << 20) ? (size_t)2 << 20 : 256;
+    const size_t o = (total + al - 1) / al * al;
+    total = o + bytes;
+    return o;
+  };
+  const size_t o_vraw = place(vbytes), o_vexp = place(tbytes), o_kin = place(kbytes),
+               o_tw = place(wbytes), o_prog = place(prog.size() * sizeof(int)),
+               o_prog1 = place(2 * sizeof(int)), o_taus = place((vc.size() + 1) * sizeof(double)),
+               o_part = place(parts * sizeof(double)), o_out = place(8 * sizeof(double));
+  if (dalloc(p, &p->d_base, total) != hipSuccess) {
     (void)hipGetLastError();
     return fail(SOP_ERR_NOMEM, "device allocation failed for the plan tables");
   }
+  char* const base = (char*)p->d_base;
+  p->d_vraw = (double*)(base + o_vraw);
+  p->d_vexp = base + o_vexp;
+  p->d_kin = base + o_kin;
+  p->d_tw = base + o_tw;
+  p->d_prog = (int*)(base + o_prog);
+  p->d_prog1 = (int*)(base + o_prog1);
+  p->d_taus = (double*)(base + o_taus);
+  p->d_part = (double*)(base + o_part);
+  p->d_out = (double*)(base + o_out);
   p->table_bytes = tbytes + kbytes;
 
   // twiddles exp(-2 pi i k/n), one block per axis
@@ -636,13 +650,14 @@ sop_status sop_plan_create_with_allocator(const sop_plan_desc* desc, void* hip_s
   std::vector<char> kinp = pack_split(kinetic_factors(p, p->ttaus), f64, p->n[0]);
   const int prog1[2] = {sop::prog_entry(sop::OP_V, 0), sop::prog_entry(sop::OP_T, 0)};
   HIPTRY(hipMemcpyAsync(p->d_vraw, desc->vtable, vbytes, hipMemcpyHostToDevice, stream));
-  HIPTRY(hipMemcpyAsync(p->d_tw, twp.data(), wbytes, hipMemcpyHostToDevice, stream));
-  HIPTRY(hipMemcpyAsync(p->d_kin, kinp.data(), kbytes, hipMemcpyHostToDevice, stream));
-  HIPTRY(hipMemcpyAsync(p->d_prog, prog.data(), prog.size() * sizeof(int), hipMemcpyHostToDevice,
-                        stream));
-  HIPTRY(hipMemcpyAsync(p->d_prog1, prog1, sizeof(prog1), hipMemcpyHostToDevice, stream));
-  HIPTRY(hipMemcpyAsync(p->d_taus, p->vtaus.data(), p->vtaus.size() * sizeof(double),
-                        hipMemcpyHostToDevice, stream));
+  // factors, twiddles, programs and taus lie next to each other: one upload
+  std::vector<char> up(o_part - o_kin, 0);
+  std::memcpy(up.data(), kinp.data(), kbytes);
+  std::memcpy(up.data() + (o_tw - o_kin), twp.data(), wbytes);
+  std::memcpy(up.data() + (o_prog - o_kin), prog.data(), prog.size() * sizeof(int));
+  std::memcpy(up.data() + (o_prog1 - o_kin), prog1, sizeof(prog1));
+  std::memcpy(up.data() + (o_taus - o_kin), p->vtaus.data(), p->vtaus.size() * sizeof(double));
+  HIPTRY(hipMemcpyAsync(base + o_kin, up.data(), up.size(), hipMemcpyHostToDevice, stream));
 
   DevView& d = p->dv;
   d.ndim = p->ndim;
@@ -773,25 +788,31 @@ sop_status sop_propagate_many(sop_plan* p, void* psi, int count, int64_t nsteps,
 
 sop_status sop_observables(sop_plan* p, const void* psi, double* out) {
   if (!p || !psi || !out) return fail(SOP_ERR_INVALID, "NULL argument");
-  sop_status st = ensure_scratch(p);
-  if (st != SOP_OK) return st;
-  const size_t bytes = (size_t)p->S * p->npts * p->csize;
-  HIPTRY(hipMemcpyAsync(p->d_scratch, psi, bytes, hipMemcpyDeviceToDevice, p->dv.stream));
+  // T_d(k) = inv_mass (hbar kappa)^2 / 2, kappa = 2 pi k / (n dx), with the
+  // 1/n of Parseval's relation along that axis
+  double c[3] = {0, 0, 0};
+  for (int a = 0; a < p->ndim; ++a) {
+    const double kap = p->hbar * 6.283185307179586476925286766559 / ((double)p->n[a] * p->dx[a]);
+    c[a] = 0.5 * p->inv_mass[a] * kap * kap / p->n[a];
+  }
+  // the last kernel writes the sums to pinned host memory (no copy to wait for)
+  if (!p->h_out && hipHostMalloc((void**)&p->h_out, 8 * sizeof(double), hipHostMallocDefault) !=
+                       hipSuccess) {
+    p->h_out = nullptr;
+    (void)hipGetLastError();
+    return fail(SOP_ERR_NOMEM, "pinned memory for the observables");
+  }
   if (p->ndim == 1)
-    HIPTRY(sop::k1d_fft_forward(p->dv, p->d_scratch));
+    HIPTRY(sop::k1d_observe(p->dv, psi, p->d_vraw, c[0], p->h_out));
   else
-    HIPTRY(sop::k3d_fft_forward(p->dv, p->d_scratch));
-  HIPTRY(sop::obs_reduce(p->dv, psi, p->d_scratch, p->d_vraw, p->inv_mass, p->dx, p->hbar,
-                         p->d_part, p->d_out));
-  double raw[8];
-  HIPTRY(hipMemcpyAsync(raw, p->d_out, (p->S + 2) * sizeof(double), hipMemcpyDeviceToHost,
-                        p->dv.stream));
+    HIPTRY(sop::k3d_observe(p->dv, psi, p->d_vraw, c, p->d_part, p->h_out));
   HIPTRY(hipStreamSynchronize(p->dv.stream));
+  const volatile double* const raw = p->h_out;
   const int S = p->S;
   double norm = 0;
   for (int s = 0; s < S; ++s) norm += raw[s] * p->dV;
   const double ev = raw[S] * p->dV;
-  const double et = raw[S + 1] * p->dV / (double)p->npts;
+  const double et = raw[S + 1] * p->dV;
   out[0] = norm;
   out[1] = et + ev;
   for (int s = 0; s < S; ++s) out[2 + s] = raw[s] * p->dV;
