@@ -265,8 +265,9 @@ sop_status tune_family(sop_batch* b, Family1& f) {
     h[i].vexp = d.vexp;
     h[i].kin = d.kin;
     h[i].tw = d.tw[0];
-    h[i].prog = d.prog;
+    h[i].prog = d.prog_1d();
     h[i].nact = d.nact;
+    h[i].mid = d.merged();
     h[i].nsteps = std::max(1, 64 / d.nact);
     h[i].conj = 0;
   }
@@ -658,8 +659,9 @@ sop_status sop_batch_propagate(sop_batch* b, void* const* psi, const int64_t* ns
         h[i].vexp = d.vexp;
         h[i].kin = d.kin;
         h[i].tw = d.tw[0];
-        h[i].prog = d.prog;
+        h[i].prog = d.prog_1d();
         h[i].nact = d.nact;
+        h[i].mid = d.merged();
         h[i].nsteps = ns[order[i]];
         h[i].conj = conj;
       }

@@ -8,7 +8,8 @@
 // the stored table exp(-i a dt V(x)/hbar) of its unique coefficient
 // (Eq. range_index_unq); a kinetic action is forward FFT -> phase (with 1/N
 // folded in) -> inverse FFT (Sec. "Dynamic Fourier method").  conj = 1
-// conjugates every table, which is U(-dt).
+// conjugates every table, which is U(-dt).  At a step boundary inside the
+// call the two adjoining actions of one kind run as one (DevView::mid).
 #pragma once
 
 #include "fft_core.hpp"
@@ -56,6 +57,49 @@ __device__ __forceinline__ int guard(int t) {
   else return t;
 }
 
+// Walk over the actions of a run of NT threads.  Plain: the program (nact
+// actions) once per step.  With merged step boundaries (mid), `prog` holds the
+// program with the merged action before its last one, a_1 .. a_{n-1} mid a_n:
+// every step but the first starts at a_2 and every step but the last ends with
+// mid.  The lanes of each wave hold a piece of the program, one entry each,
+// and the current entry is read from its lane: a load of every entry from
+// memory would stand at the head of each action's chain.
+template <int NT>
+struct Walk {
+  static constexpr int CH = NT < 64 ? NT : 64;  // entries of a piece
+  const int* prog;
+  int len, again, end, last;
+  int pos = 0, base = 0, piece;
+  int64_t left;  // actions to run
+  __device__ __forceinline__ Walk(const int* prog_, int nact, int64_t nsteps, int mid) {
+    const int body = mid ? nact - 1 : nact;  // actions a further step adds
+    prog = prog_;
+    len = mid ? nact + 1 : nact;
+    end = nact;
+    again = mid ? 1 : 0;
+    last = len - 1;
+    left = nsteps > 0 ? nsteps * body + again : 0;
+    fetch();
+  }
+  __device__ __forceinline__ void fetch() {
+    const int i = base + (int)threadIdx.x % CH;
+    piece = prog[i < len ? i : len - 1];
+  }
+  __device__ __forceinline__ int code() const {
+    return __builtin_amdgcn_readlane(piece, pos - base);
+  }
+  __device__ __forceinline__ void next() {
+    --left;
+    ++pos;
+    if (pos == end) pos = again;
+    if (left == 1) pos = last;
+    if (pos < base || pos >= base + CH) {
+      base = pos - pos % CH;
+      fetch();
+    }
+  }
+};
+
 // PL = pencils exchanged through LDS at once (S, or 1 when S pencils do not
 // fit).  `lds` holds PL padded pencils.  With one pencil of buffer and two
 // surfaces the two transforms run interleaved (fft_forward_pair).
@@ -64,10 +108,14 @@ __device__ __forceinline__ void run_1d(cx<T>* __restrict__ psi, const cx<T>* __r
                                        const cx<T>* __restrict__ kin,
                                        const cx<T>* __restrict__ tw,
                                        const int* __restrict__ prog, int nact, int64_t nsteps,
-                                       int conj, cx<T>* lds) {
+                                       int conj, int mid, cx<T>* lds) {
   const int t0 = threadIdx.x;
   constexpr int N = SC::N, E = SC::E, NE = S * (S + 1) / 2;
   const T csign = conj ? (T)-1 : (T)1;
+  // the tables of a length with a body on waves are stored in that body's order
+  constexpr int W = wave_body(N, S);
+  auto place_x = [](int x) { return W ? wave_order_x(W ? W : 1, x) : x; };
+  auto place_k = [](int k) { return W ? wave_order_k(W ? W : 1, k) : k; };
   cx<T> v[S][E];
 #pragma unroll
   for (int s = 0; s < S; ++s)
@@ -75,9 +123,9 @@ __device__ __forceinline__ void run_1d(cx<T>* __restrict__ psi, const cx<T>* __r
     for (int q = 0; q < E; ++q) v[s][q] = psi[s * N + own_idx<N, E, SC::RF>(t0, q)];
   const LayPadded lay{0, lds_pencil<SC>()};
 
-  for (int64_t step = 0; step < nsteps; ++step) {
-    for (int a = 0; a < nact; ++a) {
-      const int code = prog[a];
+  for (Walk<SC::TPC> w(prog, nact, nsteps, mid); w.left > 0; w.next()) {
+    {
+      const int code = w.code();
       const int idx = code & 0xffff;
       const int t = guard<GUARD>(t0);
       if ((code >> 16) == OP_V) {
@@ -88,7 +136,7 @@ __device__ __forceinline__ void run_1d(cx<T>* __restrict__ psi, const cx<T>* __r
           const int x = own_idx<N, E, SC::RF>(t, q);
           Fac<T> u[NE];
 #pragma unroll
-          for (int e = 0; e < NE; ++e) u[e] = load_fac(U, e * N + x, csign);
+          for (int e = 0; e < NE; ++e) u[e] = load_fac(U, e * N + place_x(x), csign);
           cx<T> w[S];
 #pragma unroll
           for (int s = 0; s < S; ++s) w[s] = v[s][q];
@@ -110,7 +158,7 @@ __device__ __forceinline__ void run_1d(cx<T>* __restrict__ psi, const cx<T>* __r
         const cx<T>* F = kin + (size_t)idx * N * Split<T>::rep;
 #pragma unroll
         for (int q = 0; q < E; ++q) {
-          const Fac<T> f = load_fac(F, own_idx<N, E, SC::RL>(t, q), csign);
+          const Fac<T> f = load_fac(F, place_k(own_idx<N, E, SC::RL>(t, q)), csign);
 #pragma unroll
           for (int s = 0; s < S; ++s) v[s][q] = fmul(v[s][q], f);
         }

@@ -315,6 +315,21 @@ __device__ __forceinline__ Fac<T> ldfac(__amdgpu_buffer_rsrc_t r, uint32_t idx, 
   }
   return F;
 }
+// The entry `bytes` past byte offset `off` of a factor table (bytes the same in
+// every lane, usually a constant).
+template <typename T>
+__device__ __forceinline__ Fac<T> ldfac_at(__amdgpu_buffer_rsrc_t r, uint32_t off, uint32_t bytes) {
+  Fac<T> F;
+  const sop_u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)(off + bytes), 0, 0);
+  if constexpr (std::is_same<T, float>::value) {
+    const sop_f32x4 q = __builtin_bit_cast(sop_f32x4, v);
+    F.w = {q.x, q.y};
+    F.lo = {q.z, q.w};
+  } else {
+    F.w = __builtin_bit_cast(cx<double>, v);
+  }
+  return F;
+}
 __device__ __forceinline__ void st(__amdgpu_buffer_rsrc_t r, uint32_t idx, cx<double> v) {
   __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(sop_u32x4, v), r, (int)(idx * 16u), 0, 0);
 }

@@ -113,6 +113,16 @@ struct DevView {
   const int* prog = nullptr;   // device copy of the step program
   int nact = 0;
   std::vector<int> hprog;      // host copy of the step program
+  // action of a step boundary inside one call: the last action of a step and
+  // the first of the next, where both are kinetic (TVT) or, on 1D grids, both
+  // potential (VTV), as one action with the summed coefficient; -1: none
+  int mid = -1;
+  // 1D: device list of a run with merged boundaries: the program with `mid`
+  // before its last action
+  const int* prog_mid = nullptr;
+  // program and flag of a 1D run
+  const int* prog_1d() const { return mid >= 0 ? prog_mid : prog; }
+  int merged() const { return mid >= 0 ? 1 : 0; }
   Timer* timer = nullptr;      // non-null while timing is enabled
   GraphCache* graphs = nullptr;  // non-null when 3D steps may be graph-captured
   int count = 1;               // states of a batch processed by each 3D launch
@@ -151,6 +161,26 @@ struct TimedLaunch {
     }
   }
 };
+
+// Two surfaces of n = 256 W points run on W waves of 64 lanes (W = 1, 2, 4, 8;
+// body_1d_waves.hpp); 0: the general body serves the length.
+__host__ __device__ constexpr int wave_body(int n, int S) {
+  return S == 2 && (n == 256 || n == 512 || n == 1024 || n == 2048) ? n / 256 : 0;
+}
+// Tables of such plans are stored in the order in which the lanes read them:
+// entry (wave w, register r, lane pair q) at (8 w + r) 32 + q, so that one load
+// of a wave is a run of 32 entries a surface instead of 16-byte pieces 16 W
+// bytes apart.  Place of point x, and of frequency k:
+__host__ __device__ inline int wave_order_x(int W, int x) {
+  const int w = x % W, h = (x / W) % 4, g = (x / (4 * W)) % 8, r = x / (32 * W);
+  return (8 * w + r) * 32 + 8 * h + g;
+}
+__host__ __device__ inline int wave_order_k(int W, int k) {
+  const int q = k % 32;  // g + 8 h
+  const int c = (k / 32) % 8;  // c2 + 2 k1''
+  const int R = (c >> 1) + 4 * (c & 1), k2 = k / 256;
+  return (8 * (R % W) + k2 + W * (R / W)) * 32 + q;
+}
 
 // kernels_1d.hip
 bool k1d_supported(int n, int S);
@@ -300,7 +330,8 @@ hipError_t interp_axis(hipStream_t s, const InterpAxis& g, bool krow);
 hipError_t interp_rows(hipStream_t s, const double* Wt, int ldw, int n, int S, int nj,
                        const double2* X, double2* out, int nd);
 // kernels_aux.hip
-// tile = 0: [u][entry][point] (1D); tile = C: the z-pass tile layout (3D).
+// tile = 0: [u][entry][point] (1D; tile = -W: the points in wave order);
+// tile = C: the z-pass tile layout (3D).
 // dmask: bit e set where V has the term *s_dev * dtab[e] (the packed entries
 // whose table is not zero everywhere); 0: V = vraw.
 hipError_t form_vexp(const DevView& d, const double* vraw_dev, const double* taus, int ntau,
@@ -337,6 +368,8 @@ struct BMember1 {
   int64_t nsteps;
   int nact;
   int conj;
+  int mid;            // merged step boundaries (prog then has the merged action before its last)
+  int pad;
 };
 // Device descriptor of one 3D member of a lockstep group
 // (kernels_batch3d.hip).  The member's program is the pruned VTV sequence

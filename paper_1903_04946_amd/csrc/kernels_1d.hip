@@ -1,7 +1,7 @@
 // kernels_1d.hip -- one-dimensional grids: the whole composed time step runs
 // inside one persistent workgroup per wavepacket (the step body is run_1d).
 #include "body_1d.hpp"
-#include "body_1d_w4.hpp"
+#include "body_1d_waves.hpp"
 #include "reduce.hpp"
 
 namespace sop {
@@ -14,23 +14,23 @@ template <typename T, class SC, int S, int PL>
 __global__ void __launch_bounds__(SC::TPC)
     k1d_prop_kernel(cx<T>* __restrict__ psi, const cx<T>* __restrict__ vexp,
                     const cx<T>* __restrict__ kin, const cx<T>* __restrict__ tw,
-                    const int* __restrict__ prog, int nact, int64_t nsteps, int conj) {
+                    const int* __restrict__ prog, int nact, int64_t nsteps, int conj, int mid) {
   extern __shared__ char smem_raw[];
   cx<T>* lds = reinterpret_cast<cx<T>*>(smem_raw);
   psi += (size_t)blockIdx.x * S * SC::N;  // one workgroup per state
-  run_1d<T, SC, S, PL>(psi, vexp, kin, tw, prog, nact, nsteps, conj, lds);
+  run_1d<T, SC, S, PL>(psi, vexp, kin, tw, prog, nact, nsteps, conj, mid, lds);
 }
 
-// Two surfaces of 1024 points: the four-wave body.
-template <typename T>
-__global__ void __launch_bounds__(w4::kThreads)
-    k1d_w4_kernel(cx<T>* __restrict__ psi, const cx<T>* __restrict__ vexp,
-                  const cx<T>* __restrict__ kin, const cx<T>* __restrict__ tw,
-                  const int* __restrict__ prog, int nact, int64_t nsteps, int conj) {
+// Two surfaces of 256 W points: the body on W waves.
+template <typename T, int W>
+__global__ void __launch_bounds__(wv::Dim<W>::threads)
+    k1d_waves_kernel(cx<T>* __restrict__ psi, const cx<T>* __restrict__ vexp,
+                     const cx<T>* __restrict__ kin, const cx<T>* __restrict__ tw,
+                     const int* __restrict__ prog, int nact, int64_t nsteps, int conj, int mid) {
   extern __shared__ char smem_raw[];
   cx<T>* lds = reinterpret_cast<cx<T>*>(smem_raw);
-  psi += (size_t)blockIdx.x * 2 * w4::N;  // one workgroup per state
-  run_1d_w4<T>(psi, vexp, kin, tw, prog, nact, nsteps, conj, lds);
+  psi += (size_t)blockIdx.x * 2 * wv::Dim<W>::N;  // one workgroup per state
+  wv::run<T, W>(psi, vexp, kin, tw, prog, nact, nsteps, conj, mid, lds);
 }
 
 // Observables of one state in one workgroup: out[0..S) = sum |psi_s|^2,
@@ -101,28 +101,29 @@ template <typename T, class SC, int S>
 hipError_t launch_prop(const DevView& d, void* psi, int64_t nsteps, int conj, int count) {
   constexpr size_t one = (size_t)lds_pencil<SC>() * sizeof(cx<T>);
   TimedLaunch tl(d, KIND_1D, 2.0 * S * SC::N * sizeof(cx<T>) * count);
-  if constexpr (SC::N == w4::N && S == 2) {
-    constexpr size_t bytes = w4::lds_bytes<T>();
-    auto k = k1d_w4_kernel<T>;
+  if constexpr (wave_body(SC::N, S) > 0) {
+    constexpr int W = wave_body(SC::N, S);
+    constexpr size_t bytes = wv::lds_bytes<T, W>();
+    auto k = k1d_waves_kernel<T, W>;
     const hipError_t e = set_lds((const void*)k, bytes);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k, dim3(count), dim3(w4::kThreads), bytes, d.stream, (cx<T>*)psi,
-                       (const cx<T>*)d.vexp, (const cx<T>*)d.kin, (const cx<T>*)d.tw[0], d.prog,
-                       d.nact, nsteps, conj);
+    hipLaunchKernelGGL(k, dim3(count), dim3(wv::Dim<W>::threads), bytes, d.stream, (cx<T>*)psi,
+                       (const cx<T>*)d.vexp, (const cx<T>*)d.kin, (const cx<T>*)d.tw[0],
+                       d.prog_1d(), d.nact, nsteps, conj, d.merged());
   } else if (one * S <= kMaxLds) {
     auto k = k1d_prop_kernel<T, SC, S, S>;
     const hipError_t e = set_lds((const void*)k, one * S);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k, dim3(count), dim3(SC::TPC), one * S, d.stream, (cx<T>*)psi,
-                       (const cx<T>*)d.vexp, (const cx<T>*)d.kin, (const cx<T>*)d.tw[0], d.prog,
-                       d.nact, nsteps, conj);
+                       (const cx<T>*)d.vexp, (const cx<T>*)d.kin, (const cx<T>*)d.tw[0], d.prog_1d(),
+                       d.nact, nsteps, conj, d.merged());
   } else {
     auto k = k1d_prop_kernel<T, SC, S, 1>;
     const hipError_t e = set_lds((const void*)k, one);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k, dim3(count), dim3(SC::TPC), one, d.stream, (cx<T>*)psi,
-                       (const cx<T>*)d.vexp, (const cx<T>*)d.kin, (const cx<T>*)d.tw[0], d.prog,
-                       d.nact, nsteps, conj);
+                       (const cx<T>*)d.vexp, (const cx<T>*)d.kin, (const cx<T>*)d.tw[0], d.prog_1d(),
+                       d.nact, nsteps, conj, d.merged());
   }
   return hipGetLastError();
 }

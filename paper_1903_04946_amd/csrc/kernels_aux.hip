@@ -119,11 +119,12 @@ __device__ __forceinline__ void jacobi_sym(double (&A)[S][S], double (&R)[S][S])
 }
 
 // Destination index of (table u, entry e, point x): structure of arrays for
-// 1D (tile = 0) or the z-pass tile layout for a cubic 3D grid of side n
+// 1D (tile = 0, or -W with the points in wave order) or the z-pass tile layout for a cubic 3D grid of side n
 // (x below 2^31: 32-bit divisions).
 __device__ __forceinline__ int64_t table_index(int64_t npts, int NE, int tile, int n, int u, int e,
                                                int64_t x) {
-  if (tile == 0) return ((int64_t)u * NE + e) * npts + x;
+  if (tile <= 0)
+    return ((int64_t)u * NE + e) * npts + (tile == 0 ? x : (int64_t)wave_order_x(-tile, (int)x));
   const uint32_t row = (uint32_t)x / (uint32_t)n, xx = (uint32_t)x - row * (uint32_t)n;
   const uint32_t z = row / (uint32_t)n, y = row - z * (uint32_t)n;
   const uint32_t tx = xx / (uint32_t)tile;

@@ -13,7 +13,7 @@
 // single-plan kernel.  All variants compute the same DFTs, in different
 // radix orders.
 #include "body_1d.hpp"
-#include "body_1d_w4.hpp"
+#include "body_1d_waves.hpp"
 
 namespace sop {
 namespace {
@@ -56,30 +56,32 @@ __global__ void __launch_bounds__(SC::TPC)
   const BMember1 m = mem[blockIdx.x];
   if (m.nsteps <= 0) return;
   run_1d<T, SC, S, PL, G>((cx<T>*)m.psi, (const cx<T>*)m.vexp, (const cx<T>*)m.kin,
-                          (const cx<T>*)m.tw, m.prog, m.nact, m.nsteps, m.conj, lds);
+                          (const cx<T>*)m.tw, m.prog, m.nact, m.nsteps, m.conj, m.mid, lds);
 }
 
-template <typename T>
-__global__ void __launch_bounds__(w4::kThreads) k1b_w4_kernel(const BMember1* __restrict__ mem) {
+template <typename T, int W>
+__global__ void __launch_bounds__(wv::Dim<W>::threads)
+    k1b_waves_kernel(const BMember1* __restrict__ mem) {
   extern __shared__ char smem_raw[];
   cx<T>* lds = reinterpret_cast<cx<T>*>(smem_raw);
   const BMember1 m = mem[blockIdx.x];
   if (m.nsteps <= 0) return;
-  run_1d_w4<T>((cx<T>*)m.psi, (const cx<T>*)m.vexp, (const cx<T>*)m.kin, (const cx<T>*)m.tw,
-               m.prog, m.nact, m.nsteps, m.conj, lds);
+  wv::run<T, W>((cx<T>*)m.psi, (const cx<T>*)m.vexp, (const cx<T>*)m.kin, (const cx<T>*)m.tw,
+                m.prog, m.nact, m.nsteps, m.conj, m.mid, lds);
 }
 
-// two surfaces of 1024 points on four waves
-hipError_t launch_w4(bool f64, const BMember1* mem, int count, hipStream_t stream) {
+// two surfaces of 256 W points on W waves
+template <int W>
+hipError_t launch_waves(bool f64, const BMember1* mem, int count, hipStream_t stream) {
   auto go = [&](auto k, size_t bytes) {
     hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize,
                                        (int)bytes);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k, dim3(count), dim3(w4::kThreads), bytes, stream, mem);
+    hipLaunchKernelGGL(k, dim3(count), dim3(wv::Dim<W>::threads), bytes, stream, mem);
     return hipGetLastError();
   };
-  if (f64) return go(k1b_w4_kernel<double>, w4::lds_bytes<double>());
-  return go(k1b_w4_kernel<float>, w4::lds_bytes<float>());
+  if (f64) return go(k1b_waves_kernel<double, W>, wv::lds_bytes<double, W>());
+  return go(k1b_waves_kernel<float, W>, wv::lds_bytes<float, W>());
 }
 
 template <typename T, class SC, int S, bool G>
@@ -124,13 +126,14 @@ hipError_t by_type(int S, bool f64, const BMember1* mem, int count, hipStream_t 
 
 // variants of one tuned length N <= 4096: 0 the default E8 schedule, 1 the
 // same with the other twiddle policy, 2 E4 and 3 E16 (recomputed twiddles);
-// N = 8192: 0 E8, 1 E16 (both recomputed).  Two surfaces of 1024 points: 0
-// the four-wave body (the single-plan kernel there), 4 the default E8.
+// N = 8192: 0 E8, 1 E16 (both recomputed).  Two surfaces of 512, 1024 or 2048
+// points: 0 the body on N / 256 waves (the single-plan kernel there), 4 the
+// default E8.
 template <int N, class DEF>
 hipError_t tuned(int variant, int S, bool f64, const BMember1* mem, int count,
                  hipStream_t stream) {
-  if constexpr (N == w4::N) {
-    if (S == 2 && variant == 0) return launch_w4(f64, mem, count, stream);
+  if constexpr (wave_body(N, 2) > 0) {
+    if (S == 2 && variant == 0) return launch_waves<wave_body(N, 2)>(f64, mem, count, stream);
     if (S == 2 && variant == 4) return by_type<DEF, G_DEFAULT>(S, f64, mem, count, stream);
   }
   if (variant == 0) return by_type<DEF, G_DEFAULT>(S, f64, mem, count, stream);
@@ -147,7 +150,7 @@ hipError_t tuned(int variant, int S, bool f64, const BMember1* mem, int count,
 }  // namespace
 
 int k1b_variants(int n, int S) {
-  if (n == w4::N && S == 2) return 5;
+  if (n > 256 && wave_body(n, S) > 0) return 5;
   switch (n) {
     case 512: case 1024: case 2048: case 4096: return 4;
     case 8192: return 2;
@@ -158,8 +161,15 @@ int k1b_variants(int n, int S) {
 
 const char* k1b_variant_name(int n, int S, int variant, bool f64) {
   const bool g = f64 ? guard_default<double>(n) : guard_default<float>(n);
-  if (n == w4::N && S == 2) {
-    if (variant == 0) return "four waves, radix 8.8.4.4 (four-step), wave-local exchanges";
+  if (wave_body(n, S) > 0) {
+    if (variant == 0) {
+      switch (n) {
+        case 256: return "one wave, radix 8.8.4 (four-step), wave-local exchanges";
+        case 512: return "two waves, radix 8.8.4.2 (four-step), wave-local exchanges";
+        case 1024: return "four waves, radix 8.8.4.4 (four-step), wave-local exchanges";
+        default: return "eight waves, radix 8.8.4.8 (four-step), wave-local exchanges";
+      }
+    }
     if (variant == 4) variant = 0;
   }
   if (variant == 0 || (variant == 1 && n <= 4096)) {
@@ -210,7 +220,9 @@ hipError_t k1b_launch(int n, int S, bool f64, int variant, const BMember1* mem, 
     case 32: return by_type<S32>(S, f64, mem, count, stream);
     case 64: return by_type<S64>(S, f64, mem, count, stream);
     case 128: return by_type<S128>(S, f64, mem, count, stream);
-    case 256: return by_type<S256>(S, f64, mem, count, stream);
+    case 256:
+      if (S == 2) return launch_waves<1>(f64, mem, count, stream);
+      return by_type<S256>(S, f64, mem, count, stream);
     case 512: return tuned<512, S512>(variant, S, f64, mem, count, stream);
     case 1024: return tuned<1024, S1024>(variant, S, f64, mem, count, stream);
     case 2048: return tuned<2048, S2048>(variant, S, f64, mem, count, stream);

@@ -221,6 +221,7 @@ struct sop_plan {
   Sequence seq;
   std::vector<double> vtaus;  // c dt / hbar of the potential tables
   std::vector<double> ttaus;  // c dt of the kinetic factor sets
+  bool tmid = false, vmid = false;  // a merged boundary action of either kind (DevView::mid)
   DevView dv;
   void* d_base = nullptr;  // the allocation that holds the buffers down to d_out
   double* d_vraw = nullptr;
@@ -245,7 +246,7 @@ struct sop_plan {
   bool eig_form = false;  // d_vexp holds the compact eigen form (3D FP64, S >= 2)
   double vbound = 0;      // max over points of max_i sum_j |V_ij| (bounds |lam|)
   std::vector<double> dvbound;  // the same for each dvtables[k]
-  int tile = 0;  // potential-table layout (0 = [u][entry][point])
+  int tile = 0;  // potential-table layout (form_vexp)
   sop::Timer* timer = nullptr;
   int nparams = 0;
   double* d_vbase = nullptr;  // V at theta = 0
@@ -323,6 +324,7 @@ void free_plan(sop_plan* p) {
 std::vector<ld> kinetic_factors(const sop_plan* p, const std::vector<double>& taus) {
   const int nax = p->ndim == 1 ? 1 : 3;
   const int nn = p->n[0];
+  const int W = p->ndim == 1 ? sop::wave_body(nn, p->S) : 0;  // stored in wave order
   std::vector<ld> out((size_t)taus.size() * nax * nn * 2);
   for (size_t u = 0; u < taus.size(); ++u)
     for (int a = 0; a < nax; ++a)
@@ -330,7 +332,8 @@ std::vector<ld> kinetic_factors(const sop_plan* p, const std::vector<double>& ta
         const int kk = (k < nn / 2) ? k : k - nn;
         const ld kap = kTwoPi * (ld)kk / ((ld)p->n[a] * (ld)p->dx[a]);
         const ld ph = -(ld)taus[u] * (ld)p->hbar * kap * kap * (ld)p->inv_mass[a] / 2.0L;
-        const size_t o = (((size_t)u * nax + a) * nn + k) * 2;
+        const int kp = W ? sop::wave_order_k(W, k) : k;
+        const size_t o = (((size_t)u * nax + a) * nn + kp) * 2;
         const ld scale = 1.0L / (ld)p->n[a];
         out[o] = std::cos(ph) * scale;
         out[o + 1] = std::sin(ph) * scale;
@@ -404,7 +407,8 @@ double param_bound(const sop_plan* p, double v0bound, const double* theta) {
 // the compact eigen form, or one exp(-i tau V) table per unique coefficient.
 hipError_t form_tables(sop_plan* p) {
   if (p->eig_form) return sop::form_eigq(p->dv, p->d_vraw, p->tile, p->d_vexp);
-  return sop::form_vexp(p->dv, p->d_vraw, p->d_taus, (int)p->vtaus.size(), p->tile, p->d_vexp);
+  return sop::form_vexp(p->dv, p->d_vraw, p->d_taus, (int)p->vtaus.size() + (p->vmid ? 1 : 0),
+                        p->tile, p->d_vexp);
 }
 
 // Rounds blocks of n interleaved extended-precision complex values to the
@@ -589,6 +593,19 @@ sop_status sop_plan_create_with_allocator(const sop_plan_desc* desc, void* hip_s
     if (j < nB) prog.push_back(sop::prog_entry(opB, q.ib[j]));
   }
 
+  // a step's last action and the next step's first, where both are of one
+  // kind: one action with the summed coefficient, a kinetic set or a (1D)
+  // potential table after the unique ones
+  const ld cmid = (ld)q.a.front() + (ld)q.a.back();
+  const bool both = nA > nB && nB > 0;  // the program begins and ends with an A action
+  p->tmid = both && !q.a_is_v;
+  p->vmid = both && q.a_is_v && p->ndim == 1;
+  std::vector<double> ktaus = p->ttaus;
+  if (p->tmid) ktaus.push_back((double)(cmid * (ld)p->dt));
+  std::vector<double> dtaus = p->vtaus;
+  dtaus.push_back((double)(cmid * (ld)p->dt / (ld)p->hbar));
+  dtaus.push_back(0.0);  // the spare one of sop_apply_action
+
   // device buffers
   const size_t vbytes = (size_t)NE * p->npts * sizeof(double);
   // 3D plans of two or three surfaces store the compact FP64 eigen form of
@@ -602,9 +619,9 @@ sop_status sop_plan_create_with_allocator(const sop_plan_desc* desc, void* hip_s
     p->eig_form = phases_fit(p, p->vbound);
   }
   const size_t tbytes = p->eig_form ? (size_t)sop::eig_slots(S) * p->npts * 2 * sizeof(double)
-                                    : vc.size() * NE * p->npts * p->csize * rep;
+                                    : (vc.size() + (p->vmid ? 1 : 0)) * NE * p->npts * p->csize * rep;
   const int nax = p->ndim == 1 ? 1 : 3;
-  const size_t kbytes = tc.size() * nax * p->n[0] * p->csize * rep;
+  const size_t kbytes = ktaus.size() * nax * p->n[0] * p->csize * rep;
   const size_t wbytes = (size_t)nax * p->n[0] * p->csize * rep;
   // one allocation for the plan's tables and small buffers
   const size_t parts = std::max((size_t)sop::kReduceBlocks * (S + 2 + sop::kMaxParams),
@@ -619,8 +636,8 @@ sop_status sop_plan_create_with_allocator(const sop_plan_desc* desc, void* hip_s
     return o;
   };
   const size_t o_vraw = place(vbytes), o_vexp = place(tbytes), o_kin = place(kbytes),
-               o_tw = place(wbytes), o_prog = place(prog.size() * sizeof(int)),
-               o_prog1 = place(2 * sizeof(int)), o_taus = place((vc.size() + 1) * sizeof(double)),
+               o_tw = place(wbytes), o_prog = place((2 * prog.size() + 1) * sizeof(int)),
+               o_prog1 = place(2 * sizeof(int)), o_taus = place(dtaus.size() * sizeof(double)),
                o_part = place(parts * sizeof(double)), o_out = place(8 * sizeof(double));
   if (dalloc(p, &p->d_base, total) != hipSuccess) {
     (void)hipGetLastError();
@@ -647,7 +664,7 @@ sop_status sop_plan_create_with_allocator(const sop_plan_desc* desc, void* hip_s
       tw[((size_t)a * p->n[0] + k) * 2 + 1] = std::sin(ang);
     }
   std::vector<char> twp = pack_split(tw, f64, p->n[0]);
-  std::vector<char> kinp = pack_split(kinetic_factors(p, p->ttaus), f64, p->n[0]);
+  std::vector<char> kinp = pack_split(kinetic_factors(p, ktaus), f64, p->n[0]);
   const int prog1[2] = {sop::prog_entry(sop::OP_V, 0), sop::prog_entry(sop::OP_T, 0)};
   HIPTRY(hipMemcpyAsync(p->d_vraw, desc->vtable, vbytes, hipMemcpyHostToDevice, stream));
   // factors, twiddles, programs and taus lie next to each other: one upload
@@ -655,8 +672,17 @@ sop_status sop_plan_create_with_allocator(const sop_plan_desc* desc, void* hip_s
   std::memcpy(up.data(), kinp.data(), kbytes);
   std::memcpy(up.data() + (o_tw - o_kin), twp.data(), wbytes);
   std::memcpy(up.data() + (o_prog - o_kin), prog.data(), prog.size() * sizeof(int));
+  const int mid = p->tmid   ? sop::prog_entry(sop::OP_T, (int)tc.size())
+                  : p->vmid ? sop::prog_entry(sop::OP_V, (int)vc.size())
+                            : -1;
+  if (mid >= 0) {  // DevView::prog_mid after the program
+    std::vector<int> list(prog);
+    list.insert(list.end() - 1, mid);
+    std::memcpy(up.data() + (o_prog - o_kin) + prog.size() * sizeof(int), list.data(),
+                list.size() * sizeof(int));
+  }
   std::memcpy(up.data() + (o_prog1 - o_kin), prog1, sizeof(prog1));
-  std::memcpy(up.data() + (o_taus - o_kin), p->vtaus.data(), p->vtaus.size() * sizeof(double));
+  std::memcpy(up.data() + (o_taus - o_kin), dtaus.data(), dtaus.size() * sizeof(double));
   HIPTRY(hipMemcpyAsync(base + o_kin, up.data(), up.size(), hipMemcpyHostToDevice, stream));
 
   DevView& d = p->dv;
@@ -674,12 +700,14 @@ sop_status sop_plan_create_with_allocator(const sop_plan_desc* desc, void* hip_s
   d.prog = p->d_prog;
   d.nact = (int)prog.size();
   d.hprog = prog;
+  d.mid = mid;
+  d.prog_mid = p->d_prog + prog.size();
   // the plane pass has one workgroup per plane and surface: it wins on small
   // grids, where the separate passes cannot fill the chip either, and loses
   // to them on 128^3 (one 139 KB workgroup per compute unit)
   d.plane = p->ndim == 3 && p->n[0] <= 64;
 
-  p->tile = p->ndim == 3 ? sop::k3d_table_tile(p->n[0], f64) : 0;
+  p->tile = p->ndim == 3 ? sop::k3d_table_tile(p->n[0], f64) : -sop::wave_body(p->n[0], S);
   d.vtaus = p->d_taus;
   d.eig = p->eig_form;
   HIPTRY(form_tables(p));
@@ -1298,16 +1326,17 @@ sop_status sop_apply_action(sop_plan* p, void* psi, int op, double coef) {
   if (op == 0) {
     const int NE = p->S * (p->S + 1) / 2;
     const double tau = (double)((ld)coef * (ld)p->dt / (ld)p->hbar);
-    HIPTRY(hipMemcpyAsync(p->d_taus + p->vtaus.size(), &tau, sizeof(double),
+    const size_t spare = p->vtaus.size() + 1;  // after the unique ones and the boundary's
+    HIPTRY(hipMemcpyAsync(p->d_taus + spare, &tau, sizeof(double),
                           hipMemcpyHostToDevice, d.stream));
     if (p->eig_form && std::fabs(tau) * p->vbound <= sop::kPhaseMax) {
       // the eigen form serves any tau within range: index the spare slot
-      d.hprog = {sop::prog_entry(sop::OP_V, (int)p->vtaus.size())};
+      d.hprog = {sop::prog_entry(sop::OP_V, (int)spare)};
     } else {
       d.eig = false;
       if (!p->d_atab)
         HIPTRY(dalloc(p, &p->d_atab, (size_t)NE * p->npts * p->csize * (d.f64 ? 1 : 2)));
-      HIPTRY(sop::form_vexp(d, p->d_vraw, p->d_taus + p->vtaus.size(), 1, p->tile, p->d_atab));
+      HIPTRY(sop::form_vexp(d, p->d_vraw, p->d_taus + spare, 1, p->tile, p->d_atab));
       d.vexp = p->d_atab;
       d.prog = p->d_prog1;
       d.hprog = {sop::prog_entry(sop::OP_V, 0)};
@@ -1324,6 +1353,7 @@ sop_status sop_apply_action(sop_plan* p, void* psi, int op, double coef) {
     d.hprog = {sop::prog_entry(sop::OP_T, 0)};
   }
   d.nact = 1;
+  d.mid = -1;
   if (p->ndim == 1)
     HIPTRY(sop::k1d_propagate(d, psi, 1, 0));
   else
@@ -1408,6 +1438,7 @@ sop_status sop_propagate_driven(sop_plan* p, void* psi, int64_t nsteps, const do
   sop::DevView d = p->dv;
   d.graphs = nullptr;
   d.nact = 1;
+  d.mid = -1;
   const size_t tab =
       (size_t)(p->S * (p->S + 1) / 2) * p->npts * p->csize * (p->dtype == SOP_C128 ? 1 : 2);
   // formation bytes per potential action: V0 and D's entries read, the table written
