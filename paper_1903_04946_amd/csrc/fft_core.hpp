@@ -34,9 +34,18 @@ template <typename T>
 __device__ __forceinline__ cx<T> cadd(cx<T> a, cx<T> b) { return {a.re + b.re, a.im + b.im}; }
 template <typename T>
 __device__ __forceinline__ cx<T> csub(cx<T> a, cx<T> b) { return {a.re - b.re, a.im - b.im}; }
+__device__ __forceinline__ double fused(double a, double b, double c) {
+  return __builtin_fma(a, b, c);
+}
+__device__ __forceinline__ float fused(float a, float b, float c) {
+  return __builtin_fmaf(a, b, c);
+}
+// The fused operation of each part is fixed: left to contraction, which of the
+// two products is fused depends on the surrounding code, and kernels that
+// share these functions would round differently.
 template <typename T>
 __device__ __forceinline__ cx<T> cmul(cx<T> a, cx<T> b) {
-  return {a.re * b.re - a.im * b.im, a.re * b.im + a.im * b.re};
+  return {fused(a.re, b.re, -(a.im * b.im)), fused(a.re, b.im, a.im * b.re)};
 }
 template <typename T>
 __device__ __forceinline__ cx<T> cconj(cx<T> a) { return {a.re, -a.im}; }
@@ -385,9 +394,23 @@ __device__ __forceinline__ void stage(cx<T> (&v)[E], int t, const cx<T>* __restr
   }
 }
 
+// What orders an exchange's LDS writes before its reads: a workgroup barrier,
+// or, where one wave owns whole pencils, a compiler fence (a wavefront's LDS
+// operations complete in issue order).
+struct BlockSync {
+  static __device__ __forceinline__ void sync() { __syncthreads(); }
+};
+struct WaveSync {
+  static __device__ __forceinline__ void sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+  }
+};
+
 // Writes the outputs of a (R, L) stage to LDS and reads the inputs of the
 // next stage (radix R2).  All P pencils of the thread go through together.
-template <typename T, int N, int E, int R, int L, int R2, int P, class Lay>
+template <typename T, int N, int E, int R, int L, int R2, int P, class Lay, class Sync = BlockSync>
 __device__ __forceinline__ void exchange(cx<T> (*v)[E], cx<T>* lds, const Lay& lay, int t) {
   constexpr int TPC = N / E;
 #pragma unroll
@@ -400,7 +423,7 @@ __device__ __forceinline__ void exchange(cx<T> (*v)[E], cx<T>* lds, const Lay& l
 #pragma unroll
       for (int m = 0; m < R; ++m) lds[lay.off(p, base + m * L)] = v[p][b * R + m];
   }
-  __syncthreads();
+  Sync::sync();
 #pragma unroll
   for (int b = 0; b < E / R2; ++b) {
     const int j = t + TPC * b;
@@ -409,18 +432,19 @@ __device__ __forceinline__ void exchange(cx<T> (*v)[E], cx<T>* lds, const Lay& l
 #pragma unroll
       for (int m = 0; m < R2; ++m) v[p][b * R2 + m] = lds[lay.off(p, j + m * (N / R2))];
   }
-  __syncthreads();
+  Sync::sync();
 }
 
-template <typename T, int N, int E, bool INV, int L, int P, class Lay, int R, int... Rest>
+template <typename T, int N, int E, bool INV, int L, int P, class Lay, class Sync, int R,
+          int... Rest>
 __device__ __forceinline__ void run_stages(cx<T> (*v)[E], cx<T>* lds, const Lay& lay,
                                            const cx<T>* __restrict__ tw, int t, RList<R, Rest...>) {
 #pragma unroll
   for (int p = 0; p < P; ++p) stage<T, N, E, R, L, INV>(v[p], t, tw);
   if constexpr (sizeof...(Rest) > 0) {
     constexpr int R2 = RHead<Rest...>::value;
-    exchange<T, N, E, R, L, R2, P>(v, lds, lay, t);
-    run_stages<T, N, E, INV, L * R, P, Lay>(v, lds, lay, tw, t, RList<Rest...>{});
+    exchange<T, N, E, R, L, R2, P, Lay, Sync>(v, lds, lay, t);
+    run_stages<T, N, E, INV, L * R, P, Lay, Sync>(v, lds, lay, tw, t, RList<Rest...>{});
   }
 }
 
@@ -544,16 +568,16 @@ __device__ __forceinline__ void fft_inverse_pair(cx<T> (*v)[SC::E], cx<T>* lds, 
 
 // Forward transform of P pencils v[0..P-1]: input in radix-RF ownership,
 // output in radix-RL ownership.
-template <class SC, int P, typename T, class Lay>
+template <class SC, int P, class Sync = BlockSync, typename T, class Lay>
 __device__ __forceinline__ void fft_forward(cx<T> (*v)[SC::E], cx<T>* lds, const Lay& lay,
                                             const cx<T>* __restrict__ tw, int t) {
-  run_stages<T, SC::N, SC::E, false, 1, P, Lay>(v, lds, lay, tw, t, typename SC::Fwd{});
+  run_stages<T, SC::N, SC::E, false, 1, P, Lay, Sync>(v, lds, lay, tw, t, typename SC::Fwd{});
 }
 // Inverse transform: input in radix-RL ownership, output in radix-RF ownership.
-template <class SC, int P, typename T, class Lay>
+template <class SC, int P, class Sync = BlockSync, typename T, class Lay>
 __device__ __forceinline__ void fft_inverse(cx<T> (*v)[SC::E], cx<T>* lds, const Lay& lay,
                                             const cx<T>* __restrict__ tw, int t) {
-  run_stages<T, SC::N, SC::E, true, 1, P, Lay>(v, lds, lay, tw, t, typename SC::Inv{});
+  run_stages<T, SC::N, SC::E, true, 1, P, Lay, Sync>(v, lds, lay, tw, t, typename SC::Inv{});
 }
 
 // ----------------------------------------------------------------- phases
@@ -569,6 +593,7 @@ constexpr double kPhaseMax = 1.0e6;
 // 1e-19).  Short and branch-free, unlike the general library routine with its
 // large-argument reduction.
 __host__ __device__ __forceinline__ void sincos_phase(double x, double* sn, double* cs) {
+#pragma clang fp contract(off)
   const double k = rint(x * 0.63661977236758138);  // 2/pi
   double r = fma(-k, 1.5707963276654482, x);      // C1 = 0x1.921fb548p+0
   r = fma(-k, -8.705515692000731e-10, r);         // C2 = -0x1.de973dc8p-31

@@ -16,6 +16,7 @@
 // z-pass (two matvecs in registers; the arithmetic is the same as two
 // separate passes).  The planner stores the three per-axis factors
 // f_d = exp(-i tau hbar kappa^2 / (2 m_d)) / n_d of each unique coefficient.
+#include <algorithm>
 #include <type_traits>
 #include <vector>
 
@@ -75,6 +76,38 @@ __global__ void __launch_bounds__(C * SC::TPC)
   zpass_body<T, SC, S, C, kTableCols, AX, EQ>(psi + off, vexp, nv, iv0, iv1, conj, tw, fz, lds,
                                               blockIdx.x, blockIdx.y, taus, (int)threadIdx.x,
                                               src ? src + off : nullptr);
+}
+
+// ---------------------------------------------------------------- z tile
+// grid (N / C, N, ceil(states / per)): `per` states a workgroup
+template <class SC>
+struct ZTile {  // lengths served by ztile_body: columns and threads of a tile
+  static constexpr int C = 0, NT = 0;
+};
+template <>
+struct ZTile<Z32> {
+  static constexpr int C = 16, NT = 256;
+};
+template <>
+struct ZTile<Z48> {
+  static constexpr int C = 16, NT = 256;
+};
+template <>
+struct ZTile<Z64> {
+  static constexpr int C = 8, NT = 256;
+};
+template <typename T, class SC, int S, int C, int NT>
+__global__ void __launch_bounds__(NT)
+    k3d_ztile(cx<T>* __restrict__ psi, int states, int per, const cx<double>* __restrict__ eig,
+              int nv, int iv0, int iv1, int conj, const cx<T>* __restrict__ tw,
+              const cx<T>* __restrict__ fz, const double* __restrict__ taus, const cx<T>* src) {
+  extern __shared__ char smem_raw[];
+  const int first = (int)blockIdx.z * per;
+  const size_t off = (size_t)first * S * ((size_t)SC::N * SC::N * SC::N);
+  ztile_body<T, SC, S, C, NT>(psi + off, states - first < per ? states - first : per, eig,
+                              taus[iv0] + (nv >= 2 ? taus[iv1] : 0.0), conj, tw, fz,
+                              reinterpret_cast<cx<T>*>(smem_raw), blockIdx.x, blockIdx.y,
+                              src ? src + off : nullptr);
 }
 
 // ---------------------------------------------------------------- adjoint z-pass
@@ -562,9 +595,33 @@ struct Passes {
   static hipError_t z(const DevView& d, cx<T>* psi, int nv, int iv0, int iv1, int tidx,
                       int conj, const cx<T>* src = nullptr) {
     if constexpr (EQ) {
+      if constexpr (AX == AX_KIN && ZTile<SC>::C > 0) {
+        if (d.eig && nv > 0) return ztile(d, psi, nv, iv0, iv1, tidx, conj, src);
+      }
       if (d.eig) return zk<AX, true>(d, psi, nv, iv0, iv1, tidx, conj, src);
     }
     return zk<AX, false>(d, psi, nv, iv0, iv1, tidx, conj, src);
+  }
+  static hipError_t ztile(const DevView& d, cx<T>* psi, int nv, int iv0, int iv1, int tidx,
+                          int conj, const cx<T>* src) {
+    constexpr int CT = ZTile<SC>::C, NT = ZTile<SC>::NT;
+    auto k = k3d_ztile<T, SC, S, CT, NT>;
+    const size_t lds = (size_t)S * CT * N * sizeof(cx<T>);
+    const hipError_t e = set_lds(k, lds);
+    if (e != hipSuccess) return e;
+    // States that share a workgroup's R and phases: as many as leave about 768
+    // workgroups, three on each compute unit; fewer would lose more in idle
+    // units than the shared work saves.  us a substep (FP32, Suzuki-4) at 1, at
+    // the rule's and at twice the rule's number of states: 32^3 x 3, 48 states:
+    // 46.5, 39.8, 46-49; 12 states: 22.0 (the rule's is 1), 23.8; 64^3 x 3, 8
+    // states: 76, 69, 65.
+    const int most = std::max(1, (int)((int64_t)d.count * (N / CT) * N / 768));
+    const int groups = (d.count + most - 1) / most, per = (d.count + groups - 1) / groups;
+    TimedLaunch tl(d, KIND_ZPASS, pass_bytes(d, nv));
+    hipLaunchKernelGGL(k, dim3(N / CT, N, (d.count + per - 1) / per), dim3(NT), lds, d.stream,
+                       psi, d.count, per, (const cx<double>*)d.vexp, nv, iv0, iv1, conj,
+                       (const cx<T>*)d.tw[0], kfac(d, tidx, 0), d.vtaus, src);
+    return hipGetLastError();
   }
   template <int AX, bool Q>
   static hipError_t zk(const DevView& d, cx<T>* psi, int nv, int iv0, int iv1, int tidx,

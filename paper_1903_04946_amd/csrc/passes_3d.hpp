@@ -158,8 +158,12 @@ __device__ __forceinline__ void axis_phase(cx<T> (*v)[SC::E], const cx<T>* __res
 // cache-policy bits of a buffer load: non-temporal
 constexpr int kCpolNT = 2;
 
+// The functions of the eigen form fix their fused operations themselves (no
+// contraction left to the compiler): several kernels inline them, and a
+// state's result must not depend on which one ran it.
 template <typename T, int S>
 __device__ __forceinline__ void rotation_from_slots(const cx<T>* q, T (&R)[S][S]) {
+#pragma clang fp contract(off)
   if constexpr (S == 2) {
     const T c = q[0].re, s = q[0].im;
     R[0][0] = c;
@@ -168,17 +172,61 @@ __device__ __forceinline__ void rotation_from_slots(const cx<T>* q, T (&R)[S][S]
     R[1][1] = c;
   } else {
     const T w = q[0].re, x = q[0].im, y = q[1].re, z = q[1].im;
-    R[0][0] = (T)1 - (T)2 * (y * y + z * z);
-    R[0][1] = (T)2 * (x * y - z * w);
-    R[0][2] = (T)2 * (x * z + y * w);
-    R[1][0] = (T)2 * (x * y + z * w);
-    R[1][1] = (T)1 - (T)2 * (x * x + z * z);
-    R[1][2] = (T)2 * (y * z - x * w);
-    R[2][0] = (T)2 * (x * z - y * w);
-    R[2][1] = (T)2 * (y * z + x * w);
-    R[2][2] = (T)1 - (T)2 * (x * x + y * y);
+    const T x2 = x + x, y2 = y + y, z2 = z + z;
+    const T wx = w * x2, wy = w * y2, wz = w * z2;
+    R[0][0] = fma(-z2, z, fma(-y2, y, (T)1));
+    R[0][1] = fma(x2, y, -wz);
+    R[0][2] = fma(x2, z, wy);
+    R[1][0] = fma(x2, y, wz);
+    R[1][1] = fma(-z2, z, fma(-x2, x, (T)1));
+    R[1][2] = fma(y2, z, -wx);
+    R[2][0] = fma(x2, z, -wy);
+    R[2][1] = fma(y2, z, wx);
+    R[2][2] = fma(-y2, y, fma(-x2, x, (T)1));
   }
 }
+
+// The eigen-form potential action at one point: R, and exp(-i tau lam) per
+// eigenvalue, from the point's slots; applied to a state in FP64.
+template <int S>
+struct EigPoint {
+  double R[S][S], cs[S], sn[S];
+  __device__ __forceinline__ void form(const cx<double> (&sl)[eig_slots(S)], double tau) {
+#pragma clang fp contract(off)
+    rotation_from_slots<double, S>(sl, R);
+    const double lam[3] = {sl[S == 3 ? 2 : 1].re, sl[S == 3 ? 2 : 1].im,
+                           S == 3 ? sl[eig_slots(S) - 1].re : 0.0};
+#pragma unroll
+    for (int k = 0; k < S; ++k) sincos_phase(tau * lam[k], &sn[k], &cs[k]);
+  }
+  // gamma = R^T psi, gamma_k *= exp(-i tau lam_k), psi = R gamma, rounded once
+  template <typename T>
+  __device__ __forceinline__ void apply(cx<T> (&w)[S]) const {
+#pragma clang fp contract(off)
+    cx<double> g[S];
+#pragma unroll
+    for (int k = 0; k < S; ++k) {
+      double re = R[0][k] * (double)w[0].re, im = R[0][k] * (double)w[0].im;
+#pragma unroll
+      for (int i = 1; i < S; ++i) {
+        re = fma(R[i][k], (double)w[i].re, re);
+        im = fma(R[i][k], (double)w[i].im, im);
+      }
+      // (re + i im) (cs - i sn)
+      g[k] = cx<double>{fma(re, cs[k], im * sn[k]), fma(im, cs[k], -(re * sn[k]))};
+    }
+#pragma unroll
+    for (int i = 0; i < S; ++i) {
+      double re = R[i][0] * g[0].re, im = R[i][0] * g[0].im;
+#pragma unroll
+      for (int k = 1; k < S; ++k) {
+        re = fma(R[i][k], g[k].re, re);
+        im = fma(R[i][k], g[k].im, im);
+      }
+      w[i] = cx<T>{(T)re, (T)im};
+    }
+  }
+};
 
 template <typename T, class SC, int S, int C, int TC, int AX, bool EQ = false>
 __device__ __forceinline__ void zpass_body(cx<T>* __restrict__ psi,
@@ -229,31 +277,14 @@ __device__ __forceinline__ void zpass_body(cx<T>* __restrict__ psi,
               rq, (int)((pt + e * TC) * 16u), 0, N >= 256 ? kCpolNT : 0);
           sl[e] = __builtin_bit_cast(cx<double>, w);
         }
-        double R[S][S];
-        rotation_from_slots<double, S>(sl, R);
-        const double lam[3] = {sl[S == 3 ? 2 : 1].re, sl[S == 3 ? 2 : 1].im,
-                               S == 3 ? sl[NE - 1].re : 0.0};
-        // gamma = R^T psi, gamma_k *= exp(-i tau lam_k) per action, psi = R gamma
-        cx<double> g[S];
+        EigPoint<S> ep;
+        ep.form(sl, tab);
+        cx<T> w[S];
 #pragma unroll
-        for (int k = 0; k < S; ++k) {
-          g[k] = cx<double>{0.0, 0.0};
+        for (int s = 0; s < S; ++s) w[s] = v[s][q];
+        ep.apply(w);
 #pragma unroll
-          for (int i = 0; i < S; ++i)
-            g[k] = cx<double>{g[k].re + R[i][k] * (double)v[i][q].re,
-                              g[k].im + R[i][k] * (double)v[i][q].im};
-          double sn, cs;
-          sincos_phase(tab * lam[k], &sn, &cs);
-          g[k] = cmul(g[k], cx<double>{cs, -sn});
-        }
-#pragma unroll
-        for (int i = 0; i < S; ++i) {
-          cx<double> a = {0.0, 0.0};
-#pragma unroll
-          for (int k = 0; k < S; ++k)
-            a = cx<double>{a.re + R[i][k] * g[k].re, a.im + R[i][k] * g[k].im};
-          v[i][q] = cx<T>{(T)a.re, (T)a.im};
-        }
+        for (int s = 0; s < S; ++s) v[s][q] = w[s];
       }
     }
   } else {
@@ -290,6 +321,85 @@ __device__ __forceinline__ void zpass_body(cx<T>* __restrict__ psi,
     const auto rs = rsrc(psi + s * npts, (uint32_t)npts);
 #pragma unroll
     for (int q = 0; q < E; ++q) st(rs, own_idx<N, E, SC::RF>(t, q) * plane + off0, v[s][q]);
+  }
+}
+
+// ---------------------------------------------------------------- z tile
+// The z-pass with a potential action in eigen form on grids of 32, 48 and 64
+// points, for `ns` states of one plan: tile of C columns, NT threads.  The
+// action's work is spread over all threads by points (C N / NT each), handed
+// over in LDS, and the transforms are then one wave per surface (C * TPC = 64
+// threads), which needs no further barrier; each wave stores its pencils.
+// R and the phases of a point are formed once for all states.
+// On these grids the z-pass is a chain of FP64 instructions, not traffic: with
+// eight (48: twelve) points and all surfaces in each of a wave's lanes
+// (zpass_body) a 32^3 x 3 pass has one wave on each compute unit, issuing
+// about 350 instructions a point and surface set.  One FP64 state, z-pass /
+// substep, before -> now: 32^3 x 3: 8.4 -> 5.5 / 13.0 -> 10.4 us; 48^3 x 2:
+// 9.9 -> 7.5 us a pass; 64^3 x 3: 13.2 -> 11.1 us.  From 96 points on the pass
+// is bound by memory and the tables by their size: zpass_body.
+// The same operations as zpass_body (EQ, AX_KIN) in the same order.
+template <typename T, class SC, int S, int C, int NT>
+__device__ __forceinline__ void ztile_body(cx<T>* __restrict__ psi, int ns,
+                                           const cx<double>* __restrict__ eig, double tau,
+                                           int conj, const cx<T>* __restrict__ tw,
+                                           const cx<T>* __restrict__ fz, cx<T>* lds, int bx,
+                                           int by, const cx<T>* src) {
+  constexpr int N = SC::N, E = SC::E, NE = eig_slots(S), TC = s3d::kTableCols;
+  static_assert(C * SC::TPC == 64 && NT >= 64 * S && (C * N) % NT == 0 && TC % C == 0, "tile");
+  constexpr int PP = C * N / NT;  // points per thread
+  constexpr uint32_t plane = (uint32_t)N * N;
+  constexpr int64_t npts = (int64_t)plane * N;
+  constexpr uint32_t tile = (uint32_t)N * NE * TC;
+  const int lane = (int)threadIdx.x;
+  const uint32_t off0 = (uint32_t)by * N + bx * C;
+  const size_t tbase = ((size_t)by * (N / TC) + (bx * C) / TC) * tile;
+  const int tcol = (bx * C) % TC + lane % C;
+  const T csign = conj ? (T)-1 : (T)1;
+  EigPoint<S> ep[PP];
+  const auto rq = rsrc(eig + tbase, tile);
+#pragma unroll
+  for (int i = 0; i < PP; ++i) {
+    const int z = lane / C + i * (NT / C);
+    cx<double> sl[NE];
+#pragma unroll
+    for (int e = 0; e < NE; ++e) sl[e] = ld<double>(rq, (uint32_t)((z * NE + e) * TC + tcol));
+    ep[i].form(sl, (double)csign * tau);
+  }
+  const int wv = lane / 64, l = lane % 64, col = l % C, t = l / C;
+  for (int m = 0; m < ns; ++m) {
+    cx<T>* const out = psi + (size_t)m * S * npts;
+    cx<T> w[PP][S];
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      const auto rs = rsrc((src ? src : psi) + ((size_t)m * S + s) * npts, (uint32_t)npts);
+#pragma unroll
+      for (int i = 0; i < PP; ++i)
+        w[i][s] = ld<T>(rs, (uint32_t)(lane / C + i * (NT / C)) * plane + off0 + lane % C);
+    }
+    if (m > 0) __syncthreads();  // the previous state's transforms are done with LDS
+#pragma unroll
+    for (int i = 0; i < PP; ++i) {
+      ep[i].apply(w[i]);
+#pragma unroll
+      for (int s = 0; s < S; ++s) lds[s * (N * C) + lane + i * NT] = w[i][s];
+    }
+    __syncthreads();
+    if (wv < S) {
+      cx<T>* const area = lds + wv * (N * C);
+      const LayStrided lay{col, 0, C};
+      cx<T> v[1][E];
+#pragma unroll
+      for (int q = 0; q < E; ++q) v[0][q] = area[own_idx<N, E, SC::RF>(t, q) * C + col];
+      WaveSync::sync();
+      fft_forward<SC, 1, WaveSync>(v, area, lay, tw, t);
+      axis_phase<T, SC, 1>(v, fz, csign, t);
+      fft_inverse<SC, 1, WaveSync>(v, area, lay, tw, t);
+      const auto rs = rsrc(out + wv * npts, (uint32_t)npts);
+#pragma unroll
+      for (int q = 0; q < E; ++q)
+        st(rs, own_idx<N, E, SC::RF>(t, q) * plane + off0 + col, v[0][q]);
+    }
   }
 }
 

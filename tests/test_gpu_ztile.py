@@ -1,0 +1,64 @@
+"""The z-pass of small 3D grids, whose tiles serve several states of a call:
+counts on both sides of where states begin to share a workgroup, with a last
+workgroup that holds fewer, against each state alone and against the oracle."""
+import sys
+
+import numpy as np
+import pytest
+
+from paper_1903_04946_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True)
+def announce(request):
+    print(f"\n[gpu-case] {request.node.nodeid}", flush=True)
+    sys.stdout.flush()
+    yield
+
+
+@pytest.fixture(scope="module")
+def torch_cuda():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1903_04946_amd import soprop
+    soprop.lib()
+    return torch
+
+
+@pytest.mark.parametrize("n,counts", [(32, (1, 12, 13, 25, 37)), (48, (1, 2, 11)),
+                                      (64, (1, 2, 3, 5))])
+@pytest.mark.parametrize("S", [2, 3])
+@pytest.mark.parametrize("c64", [False, True])
+def test_states_of_a_tile(torch_cuda, orc, n, counts, S, c64):
+    """Each state of a call bitwise the same as alone (the same operations in
+    the same order); one state against the oracle to 1e-12 (FP64) and 5e-6
+    (FP32: 3 steps of 3 substeps), and back again to twice that."""
+    torch = torch_cuda
+    from paper_1903_04946_amd import soprop
+    m = synth.random_small([n] * 3, S, seed=n + S)
+    dtype = torch.complex64 if c64 else torch.complex128
+    plan = soprop.Plan.from_model(m, comp="triple_jump", order=4, dt=0.02, dtype=dtype)
+    base = synth.random_state(m.psi0.shape, seed=9)
+    one = torch.from_numpy(base).to(dtype).cuda()
+    plan.propagate(one, 3)
+    prob = orc.Problem(m.n, m.lo, m.hi, m.nsurf, m.inv_mass, m.vtable, m.hbar)
+    ref = orc.propagate(prob, base, 0, 1, 4, 0.02, 3)  # VTV, triple jump, order 4
+    tol = 5e-6 if c64 else 1e-12
+    err = np.linalg.norm(one.cpu().numpy() - ref) / np.linalg.norm(ref)
+    print(f"[ztile {n}^3 x {S}] {err:.2e}")
+    assert err < tol
+    back = one.clone()
+    plan.propagate(back, 3, -1)
+    err = np.linalg.norm(back.cpu().numpy() - base) / np.linalg.norm(base)
+    assert err < 2 * tol
+    for count in counts:
+        psi = torch.from_numpy(np.stack([synth.random_state(m.psi0.shape, seed=20 + i)
+                                         for i in range(count)])).to(dtype).cuda()
+        want = psi.clone()
+        for i in range(count):
+            plan.propagate(want[i], 2)
+        plan.propagate_many(psi, 2)
+        assert torch.equal(psi, want), count
