@@ -249,12 +249,33 @@ __device__ __forceinline__ void dft16(cx<T>* v) {
   }
 }
 
+// 12 = 3 x 4 without twiddles (prime factor map: n = 4 n1 + 3 n2,
+// k = 4 k1 + 9 k2, both mod 12, makes nk = 4 n1 k1 + 3 n2 k2 mod 12)
+template <bool INV, typename T>
+__device__ __forceinline__ void dft12(cx<T>* v) {
+  cx<T> c[4][3];
+#pragma unroll
+  for (int n2 = 0; n2 < 4; ++n2) {
+#pragma unroll
+    for (int n1 = 0; n1 < 3; ++n1) c[n2][n1] = v[(4 * n1 + 3 * n2) % 12];
+    dft3<INV>(c[n2]);
+  }
+#pragma unroll
+  for (int k1 = 0; k1 < 3; ++k1) {
+    cx<T> r[4] = {c[0][k1], c[1][k1], c[2][k1], c[3][k1]};
+    dft4<INV>(r);
+#pragma unroll
+    for (int k2 = 0; k2 < 4; ++k2) v[(4 * k1 + 9 * k2) % 12] = r[k2];
+  }
+}
+
 template <int R, bool INV, typename T>
 __device__ __forceinline__ void dft(cx<T>* v) {
   if constexpr (R == 2) dft2<INV>(v);
   else if constexpr (R == 3) dft3<INV>(v);
   else if constexpr (R == 4) dft4<INV>(v);
   else if constexpr (R == 8) dft8<INV>(v);
+  else if constexpr (R == 12) dft12<INV>(v);
   else if constexpr (R == 16) dft16<INV>(v);
   else static_assert(R == 2, "unsupported radix");
 }
@@ -578,6 +599,83 @@ template <class SC, int P, class Sync = BlockSync, typename T, class Lay>
 __device__ __forceinline__ void fft_inverse(cx<T> (*v)[SC::E], cx<T>* lds, const Lay& lay,
                                             const cx<T>* __restrict__ tw, int t) {
   run_stages<T, SC::N, SC::E, true, 1, P, Lay, Sync>(v, lds, lay, tw, t, typename SC::Inv{});
+}
+
+// The twiddles of a transform's stages after the first, held in registers: read
+// ahead of the data, and once for both directions where they are the same
+// (two equal radices), they leave the chain of LDS reads between stages.  For
+// kernels of few waves, whose transforms wait for each read.
+template <int E, class Rs>
+constexpr int tw_count = 0;
+template <int E, int R, int R2, int... Rest>
+constexpr int tw_count<E, RList<R, R2, Rest...>> =
+    E / R2 * (R2 - 1) + tw_count<E, RList<R2, Rest...>>;
+template <typename T, int N, int E, int L, int O, int R>
+__device__ __forceinline__ void load_tw(Fac<T>*, const cx<T>* __restrict__, int, RList<R>) {}
+template <typename T, int N, int E, int L, int O, int R, int R2, int... Rest>
+__device__ __forceinline__ void load_tw(Fac<T>* r, const cx<T>* __restrict__ tw, int t,
+                                        RList<R, R2, Rest...>) {
+  constexpr int L2 = L * R;
+#pragma unroll
+  for (int b = 0; b < E / R2; ++b)
+#pragma unroll
+    for (int m = 1; m < R2; ++m)
+      r[O + b * (R2 - 1) + m - 1] =
+          load_fac(tw, ((t + N / E * b) % L2 * m) * (N / (L2 * R2)), (T)1);
+  load_tw<T, N, E, L2, O + E / R2 * (R2 - 1)>(r, tw, t, RList<R2, Rest...>{});
+}
+template <typename T, class SC>
+struct TwRegs {
+  static constexpr bool shared = std::is_same<typename SC::Fwd, RList<SC::RF, SC::RF>>::value;
+  Fac<T> f[tw_count<SC::E, typename SC::Fwd>], i[shared ? 1 : tw_count<SC::E, typename SC::Inv>];
+  __device__ __forceinline__ void load(const cx<T>* __restrict__ tw, int t) {
+    load_tw<T, SC::N, SC::E, 1, 0>(f, tw, t, typename SC::Fwd{});
+    if constexpr (!shared) load_tw<T, SC::N, SC::E, 1, 0>(i, tw, t, typename SC::Inv{});
+  }
+  __device__ __forceinline__ const Fac<T>* inv() const { return shared ? f : i; }
+};
+template <bool INV>
+__device__ __forceinline__ Fac<double> conj_if(Fac<double> F) {
+  if (INV) F.w.im = -F.w.im;
+  return F;
+}
+template <bool INV>
+__device__ __forceinline__ Fac<float> conj_if(Fac<float> F) {
+  if (INV) F.w.im = -F.w.im, F.lo.im = -F.lo.im;
+  return F;
+}
+// run_stages() for one pencil with its twiddles in registers (w = those of the
+// stages from this one on; the first stage has none)
+template <typename T, int N, int E, bool INV, int L, class Lay, class Sync, int R, int... Rest>
+__device__ __forceinline__ void run_stages_tw(cx<T> (*v)[E], cx<T>* lds, const Lay& lay,
+                                              const Fac<T>* w, int t, RList<R, Rest...>) {
+  constexpr int NW = L > 1 ? E / R * (R - 1) : 0;
+#pragma unroll
+  for (int b = 0; b < E / R; ++b) {
+    if constexpr (L > 1) {
+#pragma unroll
+      for (int m = 1; m < R; ++m)
+        v[0][b * R + m] = fmul(v[0][b * R + m], conj_if<INV>(w[b * (R - 1) + m - 1]));
+    }
+    dft<R, INV>(&v[0][b * R]);
+  }
+  if constexpr (sizeof...(Rest) > 0) {
+    constexpr int R2 = RHead<Rest...>::value;
+    exchange<T, N, E, R, L, R2, 1, Lay, Sync>(v, lds, lay, t);
+    run_stages_tw<T, N, E, INV, L * R, Lay, Sync>(v, lds, lay, w + NW, t, RList<Rest...>{});
+  }
+}
+// fft_forward / fft_inverse of one pencil with TwRegs
+template <class SC, class Sync, typename T, class Lay>
+__device__ __forceinline__ void fft_forward(cx<T> (*v)[SC::E], cx<T>* lds, const Lay& lay,
+                                            const TwRegs<T, SC>& tw, int t) {
+  run_stages_tw<T, SC::N, SC::E, false, 1, Lay, Sync>(v, lds, lay, tw.f, t, typename SC::Fwd{});
+}
+template <class SC, class Sync, typename T, class Lay>
+__device__ __forceinline__ void fft_inverse(cx<T> (*v)[SC::E], cx<T>* lds, const Lay& lay,
+                                            const TwRegs<T, SC>& tw, int t) {
+  run_stages_tw<T, SC::N, SC::E, true, 1, Lay, Sync>(v, lds, lay, tw.inv(), t,
+                                                     typename SC::Inv{});
 }
 
 // ----------------------------------------------------------------- phases

@@ -81,21 +81,29 @@ __global__ void __launch_bounds__(C * SC::TPC)
 // ---------------------------------------------------------------- z tile
 // grid (N / C, N, ceil(states / per)): `per` states a workgroup
 template <class SC>
-struct ZTile {  // lengths served by ztile_body: columns and threads of a tile
-  static constexpr int C = 0, NT = 0;
+struct ZTile {  // columns of a tile for lengths served by ztile_body, of few states
+  static constexpr int C = 0, few = 0;
 };
+// 32^3: 16 columns make 64 tiles of a state, on a quarter of the compute units;
+// 8 columns while the 16-column tiles of a call do not reach all of them (one
+// FP64 state, 3 surfaces: 5.35 -> 4.45 us a pass; 48 FP32 states would lose,
+// 23 -> 39 us: 64-byte pieces).  48^3 has 144 tiles of 16 columns; 8 columns
+// cost there (S = 2: 6.6 -> 9.8 us).
 template <>
 struct ZTile<Z32> {
-  static constexpr int C = 16, NT = 256;
+  static constexpr int C = 16, few = 8;
 };
 template <>
 struct ZTile<Z48> {
-  static constexpr int C = 16, NT = 256;
+  static constexpr int C = 16, few = 16;
 };
 template <>
 struct ZTile<Z64> {
-  static constexpr int C = 8, NT = 256;
+  static constexpr int C = 8, few = 8;
 };
+// 256 threads: twice as many (fewer points each) cost more in barriers than
+// they hide (32^3 x 48 FP32: 23 -> 29 us; 48^3: 6.6 -> 7.5 us; 64^3: the same).
+constexpr int kZTileThreads = 256;
 template <typename T, class SC, int S, int C, int NT>
 __global__ void __launch_bounds__(NT)
     k3d_ztile(cx<T>* __restrict__ psi, int states, int per, const cx<double>* __restrict__ eig,
@@ -604,7 +612,15 @@ struct Passes {
   }
   static hipError_t ztile(const DevView& d, cx<T>* psi, int nv, int iv0, int iv1, int tidx,
                           int conj, const cx<T>* src) {
-    constexpr int CT = ZTile<SC>::C, NT = ZTile<SC>::NT;
+    constexpr int CT = ZTile<SC>::C, CF = ZTile<SC>::few;
+    if (CF != CT && (int64_t)d.count * (N / CT) * N < 256)
+      return ztile_c<CF>(d, psi, nv, iv0, iv1, tidx, conj, src);
+    return ztile_c<CT>(d, psi, nv, iv0, iv1, tidx, conj, src);
+  }
+  template <int CT>
+  static hipError_t ztile_c(const DevView& d, cx<T>* psi, int nv, int iv0, int iv1, int tidx,
+                            int conj, const cx<T>* src) {
+    constexpr int NT = kZTileThreads;
     auto k = k3d_ztile<T, SC, S, CT, NT>;
     const size_t lds = (size_t)S * CT * N * sizeof(cx<T>);
     const hipError_t e = set_lds(k, lds);

@@ -29,7 +29,7 @@ namespace sop {
 namespace s3d {
 
 using Z32 = Sched<32, 8, RList<8, 4>, RList<4, 8>, 8, 4>;
-using Z48 = Sched<48, 12, RList<4, 4, 3>, RList<3, 4, 4>, 4, 3>;
+using Z48 = Sched<48, 12, RList<12, 4>, RList<4, 12>, 12, 4>;
 using Z64 = Sched<64, 8, RList<8, 8>, RList<8, 8>, 8, 8>;
 using Z128 = Sched<128, 8, RList<8, 4, 4>, RList<4, 4, 8>, 8, 4>;
 using Z256 = Sched<256, 8, RList<8, 8, 4>, RList<4, 8, 8>, 8, 4>;
@@ -334,10 +334,9 @@ __device__ __forceinline__ void zpass_body(cx<T>* __restrict__ psi,
 // On these grids the z-pass is a chain of FP64 instructions, not traffic: with
 // eight (48: twelve) points and all surfaces in each of a wave's lanes
 // (zpass_body) a 32^3 x 3 pass has one wave on each compute unit, issuing
-// about 350 instructions a point and surface set.  One FP64 state, z-pass /
-// substep, before -> now: 32^3 x 3: 8.4 -> 5.5 / 13.0 -> 10.4 us; 48^3 x 2:
-// 9.9 -> 7.5 us a pass; 64^3 x 3: 13.2 -> 11.1 us.  From 96 points on the pass
-// is bound by memory and the tables by their size: zpass_body.
+// about 350 instructions a point and surface set.  us a pass, one FP64
+// state, zpass_body -> now: 32^3 x 3: 8.4 -> 4.5, 48^3 x 2: 9.9 -> 6.6, 64^3 x
+// 3: 13.2 -> 9.8.  From 128 points on the pass is bound by memory: zpass_body.
 // The same operations as zpass_body (EQ, AX_KIN) in the same order.
 template <typename T, class SC, int S, int C, int NT>
 __device__ __forceinline__ void ztile_body(cx<T>* __restrict__ psi, int ns,
@@ -346,7 +345,8 @@ __device__ __forceinline__ void ztile_body(cx<T>* __restrict__ psi, int ns,
                                            const cx<T>* __restrict__ fz, cx<T>* lds, int bx,
                                            int by, const cx<T>* src) {
   constexpr int N = SC::N, E = SC::E, NE = eig_slots(S), TC = s3d::kTableCols;
-  static_assert(C * SC::TPC == 64 && NT >= 64 * S && (C * N) % NT == 0 && TC % C == 0, "tile");
+  constexpr int FT = C * SC::TPC;  // threads of one surface's transforms
+  static_assert(64 % FT == 0 && NT >= FT * S && (C * N) % NT == 0 && TC % C == 0, "tile");
   constexpr int PP = C * N / NT;  // points per thread
   constexpr uint32_t plane = (uint32_t)N * N;
   constexpr int64_t npts = (int64_t)plane * N;
@@ -356,20 +356,15 @@ __device__ __forceinline__ void ztile_body(cx<T>* __restrict__ psi, int ns,
   const size_t tbase = ((size_t)by * (N / TC) + (bx * C) / TC) * tile;
   const int tcol = (bx * C) % TC + lane % C;
   const T csign = conj ? (T)-1 : (T)1;
-  EigPoint<S> ep[PP];
   const auto rq = rsrc(eig + tbase, tile);
+  cx<double> sl[PP][NE];
 #pragma unroll
-  for (int i = 0; i < PP; ++i) {
-    const int z = lane / C + i * (NT / C);
-    cx<double> sl[NE];
+  for (int i = 0; i < PP; ++i)
 #pragma unroll
-    for (int e = 0; e < NE; ++e) sl[e] = ld<double>(rq, (uint32_t)((z * NE + e) * TC + tcol));
-    ep[i].form(sl, (double)csign * tau);
-  }
-  const int wv = lane / 64, l = lane % 64, col = l % C, t = l / C;
-  for (int m = 0; m < ns; ++m) {
-    cx<T>* const out = psi + (size_t)m * S * npts;
-    cx<T> w[PP][S];
+    for (int e = 0; e < NE; ++e)
+      sl[i][e] = ld<double>(rq, (uint32_t)(((lane / C + i * (NT / C)) * NE + e) * TC + tcol));
+  cx<T> w[PP][S];
+  auto fetch = [&](int m) {  // the thread's points of state m
 #pragma unroll
     for (int s = 0; s < S; ++s) {
       const auto rs = rsrc((src ? src : psi) + ((size_t)m * S + s) * npts, (uint32_t)npts);
@@ -377,6 +372,15 @@ __device__ __forceinline__ void ztile_body(cx<T>* __restrict__ psi, int ns,
       for (int i = 0; i < PP; ++i)
         w[i][s] = ld<T>(rs, (uint32_t)(lane / C + i * (NT / C)) * plane + off0 + lane % C);
     }
+  };
+  fetch(0);  // arrives while R and the phases are formed
+  const int wv = lane / FT, l = lane % FT, col = l % C, t = l / C;
+  EigPoint<S> ep[PP];
+#pragma unroll
+  for (int i = 0; i < PP; ++i) ep[i].form(sl[i], (double)csign * tau);
+  for (int m = 0; m < ns; ++m) {
+    cx<T>* const out = psi + (size_t)m * S * npts;
+    if (m > 0) fetch(m);
     if (m > 0) __syncthreads();  // the previous state's transforms are done with LDS
 #pragma unroll
     for (int i = 0; i < PP; ++i) {
@@ -463,11 +467,20 @@ __device__ __forceinline__ void xpass_body(cx<T>* __restrict__ psi_s,
 // ---------------------------------------------------------------- xy plane
 // The y- and x-passes of one kinetic action fused for grids whose whole xy
 // plane fits in LDS: block = one plane z of one surface, N x TPC threads.
-// The y round trip runs in the column layout (lane -> x = lane % N,
-// t = lane / N), one LDS transpose moves the plane to the row layout
-// (lane -> t = lane % TPC, y = lane / TPC), where the x round trip runs and
-// the rows are stored.  Every pencil sees the same stages, twiddles and
-// factors as in the separate passes, so the values are identical.
+// The y round trip runs in the column layout (a wave holds 64 / TPC columns),
+// one LDS transpose moves the plane to the row layout (lane -> t = lane % TPC,
+// y = lane / TPC), where the x round trip runs and the rows are stored.  Every
+// pencil sees the same stages, twiddles and factors as in the separate passes,
+// so the values are identical.
+// A single state has fewer planes than there are compute units (32^3 x 3: 96
+// of 2 waves), so the pass is the time of one plane: a chain of loads, LDS
+// round trips and butterflies.  A wave owns whole pencils in both layouts, so
+// that only the transpose needs barriers; the tables are loaded before the
+// data and staged while these arrive; twiddles are held in registers (64^3:
+// 12.5 -> 11.9 us, 48^3: 8.1 -> 7.7 us against reads between the stages); 48
+// points take two stages, 12 x 4, not 4 x 4 x 3.  us a pass (FP64), before ->
+// now: 32^3 x 3: 4.8 -> 4.5, 48^3 x 2: 10.4 -> 7.7, 64^3 x 3: 12.6 -> 11.9
+// (of which a copy of the same data takes 2.7, 4.6 and 7.4).
 template <typename T, class SC>
 constexpr size_t plane_lds_elems() {
   return (size_t)SC::N * (SC::N + SC::N / 16) + 4 * axis_block<T, SC::N>();
@@ -486,7 +499,9 @@ __device__ __forceinline__ void plane_body(cx<T>* __restrict__ psi_s,
   constexpr int N = SC::N, E = SC::E, TPC = SC::TPC;
   constexpr int P = N + N / 16;  // padded row stride in LDS
   const int lane = threadIdx.x;
-  const int col = lane % N, tc = lane / N;    // column layout
+  // column layout: a wave holds 64 / TPC whole columns
+  constexpr int CW = 64 / TPC;
+  const int col = lane / 64 * CW + lane % CW, tc = lane % 64 / CW;
   const int tr = lane % TPC, row = lane / TPC;  // row layout
   constexpr int64_t plane = (int64_t)N * N;
   const auto base = rsrc(psi_s + z * plane, (uint32_t)plane);
@@ -494,28 +509,39 @@ __device__ __forceinline__ void plane_body(cx<T>* __restrict__ psi_s,
   // staged [twiddles y | twiddles x | f_y | f_x] after the plane
   cx<T>* const twy = lds + N * P;
   cx<T>* const twx = twy + AS;
-  stage_blocks<T, N, 4>(twy, {tw + AS, tw + 2 * AS, kin + AS, kin + 2 * AS}, lane, N * TPC);
+  // the two axes' twiddles and factors, one 16-byte entry a thread
+  static_assert(4 * N <= N * TPC, "one entry a thread");
+  const sop_u32x4* const p16 =
+      reinterpret_cast<const sop_u32x4*>(lane < 2 * N ? tw : kin - 2 * AS) + N + lane;
+  sop_u32x4 entry = {};
+  if (lane < 4 * N) entry = *p16;
+  cx<T> v[1][E];
+#pragma unroll
+  for (int q = 0; q < E; ++q) v[0][q] = ld<T>(base, own_idx<N, E, SC::RF>(tc, q) * N + col);
+  if (lane < 4 * N) reinterpret_cast<sop_u32x4*>(twy)[lane] = entry;
   const LayStrided lcol{col, 0, N};
   const LayPadded lrow{row * P, 0};
   const T csign = conj ? (T)-1 : (T)1;
-  cx<T> v[1][E];
+  __syncthreads();
   // y round trip (columns)
-#pragma unroll
-  for (int q = 0; q < E; ++q) v[0][q] = ld<T>(base, own_idx<N, E, SC::RF>(tc, q) * N + col);
-  fft_forward<SC, 1>(v, lds, lcol, twy, tc);
+  TwRegs<T, SC> tws;
+  tws.load(twy, tc);
+  fft_forward<SC, WaveSync>(v, lds, lcol, tws, tc);
   axis_phase<T, SC, 1>(v, twy + 2 * AS, csign, tc);
-  fft_inverse<SC, 1>(v, lds, lcol, twy, tc);
+  fft_inverse<SC, WaveSync>(v, lds, lcol, tws, tc);
+  __syncthreads();
   // columns -> rows
 #pragma unroll
   for (int q = 0; q < E; ++q) lds[own_idx<N, E, SC::RF>(tc, q) * P + col] = v[0][q];
+  tws.load(twx, tr);
   __syncthreads();
 #pragma unroll
   for (int q = 0; q < E; ++q) v[0][q] = lds[row * P + own_idx<N, E, SC::RF>(tr, q)];
-  __syncthreads();
+  WaveSync::sync();
   // x round trip (rows)
-  fft_forward<SC, 1>(v, lds, lrow, twx, tr);
+  fft_forward<SC, WaveSync>(v, lds, lrow, tws, tr);
   axis_phase<T, SC, 1>(v, twy + 3 * AS, csign, tr);
-  fft_inverse<SC, 1>(v, lds, lrow, twx, tr);
+  fft_inverse<SC, WaveSync>(v, lds, lrow, tws, tr);
 #pragma unroll
   for (int q = 0; q < E; ++q) st(base, row * N + own_idx<N, E, SC::RF>(tr, q), v[0][q]);
 }

@@ -28,7 +28,7 @@ def torch_cuda():
     return torch
 
 
-@pytest.mark.parametrize("n,counts", [(32, (1, 12, 13, 25, 37)), (48, (1, 2, 11)),
+@pytest.mark.parametrize("n,counts", [(32, (1, 3, 4, 12, 25, 37)), (48, (1, 2, 11)),
                                       (64, (1, 2, 3, 5))])
 @pytest.mark.parametrize("S", [2, 3])
 @pytest.mark.parametrize("c64", [False, True])
