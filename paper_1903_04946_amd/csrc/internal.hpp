@@ -199,6 +199,7 @@ struct AdjointView {
   double* qacc = nullptr;       // packed gradient accumulator, S(S+1)/2 doubles a point,
                                 // [tile (y, x/C)][z][entry][x % C], C = k3d_adjoint_cols
   const double* taus = nullptr; // c dt / hbar of each potential table
+  const double* weights = nullptr;    // [S] of L = sum_s w_s P_s
   const void* checkpoints = nullptr;  // [ncp][S][npts] complex, psi at steps 0, K, 2K, ...
 };
 
@@ -347,13 +348,19 @@ hipError_t form_eig(const DevView& d, const double* vraw_dev, int tile, void* ou
 hipError_t form_eigq(const DevView& d, const double* vraw_dev, int tile, void* out,
                      const double* dtab = nullptr, unsigned dmask = 0,
                      const double* s_dev = nullptr);
+// The packed entries of each parameter table that are not zero everywhere: bit
+// e of m[k].  The others are not read (a coupling has one entry of six).
+constexpr int kMaxParams = 8;
+struct EntryMasks {
+  unsigned m[kMaxParams] = {};
+};
 hipError_t set_vparams(const DevView& d, double* vraw, const double* vbase, const double* dv,
-                       const double* delta_dev, int nparams);
+                       const EntryMasks& mask, const double* delta_dev, int nparams);
 hipError_t adjoint_seed(const DevView& d, void* lam, const void* psi, const double* w_dev,
                         double* qacc);
 // qacc in the accumulator's tile layout with `cols` columns per tile
 hipError_t grad_reduce(const DevView& d, const double* qacc, int cols, const double* dv,
-                       int nparams, double* partials, double* out_dev);
+                       const EntryMasks& mask, int nparams, double* partials, double* out_dev);
 // out_dev[0..S) = sum |psi_s|^2, out_dev[S] = sum psi^dag V psi (raw sums)
 hipError_t pops_reduce(const DevView& d, const void* psi, const double* vraw_dev,
                        double* partials, double* out_dev);
@@ -452,7 +459,6 @@ hipError_t k3q_launch(int n, int S, bool f64, const BMember3* mem, int count,
                       const QRound* rounds, int nrounds, int64_t tickets,
                       unsigned long long* ctrl, long long spin_limit, hipStream_t stream);
 
-constexpr int kMaxParams = 8;
 constexpr int kReduceBlocks = 1024;
 static_assert(kT3Partials == 9 * kReduceBlocks, "trapezoid partial buffers");
 constexpr int kReduceThreads = 256;

@@ -144,12 +144,24 @@ __global__ void __launch_bounds__(NT)
 // The pass tile is C columns of the TC-column table tiles (C divides TC).
 // Two waves per SIMD: with six pencils of state the three-surface pass needs
 // about 200-250 VGPRs, and a one-wave budget let the compiler take more.
-template <class SC, int S, int C, int TC, bool KZ>
+// Without KZ the pass moves its 738 MB (128^3 x 3) at 5.3 TB/s, 139 us.  With
+// KZ the transforms take S pencils through an exchange (a third of the
+// barriers, a third of the twiddle reads) and read their tables from LDS:
+// 182 -> 167 us.
+// The first pass of a sweep (ADJ_SEED) forms lambda = w psi and the accumulator
+// itself, and where a step boundary with a stored psi follows a pass's first
+// action (ADJ_CKPT) psi is taken from there: both spare passes of their own
+// (33 + 15 us for the seed; 139 us for an action alone and 36 us for a copy at
+// a stored step).  They are variants of their own because as run-time choices
+// they cost every pass its registers (167 -> 193 us).
+enum { ADJ_PLAIN = 0, ADJ_SEED = 1, ADJ_CKPT = 2 };
+template <class SC, int S, int C, int TC, bool KZ, int EDGE>
 __global__ void __launch_bounds__(C * SC::TPC) __attribute__((amdgpu_waves_per_eu(2)))
     k3d_zpass_adj(cx<double>* __restrict__ stk, const cx<double>* __restrict__ eig,
                   double* __restrict__ qacc,
                   const double* __restrict__ taus, int nv, int iv0, int iv1,
-                  const cx<double>* __restrict__ tw, const cx<double>* __restrict__ fz) {
+                  const cx<double>* __restrict__ tw, const cx<double>* __restrict__ fz,
+                  const double* __restrict__ w, const cx<double>* __restrict__ ckpt) {
   static_assert(TC % C == 0, "pass tile must divide the table tile");
   extern __shared__ char smem_raw[];
   cx<double>* lds = reinterpret_cast<cx<double>*>(smem_raw);
@@ -164,17 +176,30 @@ __global__ void __launch_bounds__(C * SC::TPC) __attribute__((amdgpu_waves_per_e
   const uint32_t off0 = (uint32_t)y * N + x;
   const int tcol = (blockIdx.x * C) % TC + col;  // column within the table tile
   const size_t tbase = ((size_t)y * (N / TC) + (blockIdx.x * C) / TC) * tile;
-  const LayStrided lay{col, 0, C};
+  const LayStrided lay{col, C * N, C};
+  cx<double>* const tws = lds + S * C * N;  // staged twiddles and z factor
+  if constexpr (KZ) stage_blocks<double, N, 2>(tws, {tw, fz}, lane, C * SC::TPC);
   double* const qbase = qacc + ((size_t)y * (N / C) + blockIdx.x) * ((size_t)N * NE * C) + col;
   cx<double> v[P][E];
+  auto fetch = [&](int first, const cx<double>* src) {  // S pencils from slot `first`
 #pragma unroll
-  for (int s = 0; s < P; ++s) {
-    const auto rs = rsrc(stk + s * npts, (uint32_t)npts);
+    for (int s = 0; s < S; ++s) {
+      const auto rs = rsrc(src + s * npts, (uint32_t)npts);
 #pragma unroll
-    for (int q = 0; q < E; ++q)
-      v[s][q] = ld<double>(rs, own_idx<N, E, SC::RF>(t, q) * plane + off0);
+      for (int q = 0; q < E; ++q)
+        v[first + s][q] = ld<double>(rs, own_idx<N, E, SC::RF>(t, q) * plane + off0);
+    }
+  };
+  fetch(0, stk);
+  if constexpr (EDGE == ADJ_SEED) {
+#pragma unroll
+    for (int s = 0; s < S; ++s)
+#pragma unroll
+      for (int q = 0; q < E; ++q) v[S + s][q] = cx<double>{w[s] * v[s][q].re, w[s] * v[s][q].im};
+  } else {
+    fetch(S, stk + S * npts);
   }
-  auto vact = [&](int iv) {
+  auto vact = [&](int iv, auto init) {
     const auto rg = rsrc(eig + tbase, tile);
     const double tau = taus[iv];
 #pragma unroll
@@ -285,7 +310,9 @@ __global__ void __launch_bounds__(C * SC::TPC) __attribute__((amdgpu_waves_per_e
             qij += tq[i][b] * ev[j * S + b];
             qji += tq[j][b] * ev[i * S + b];
           }
-          qp0[e * C] += (i == j) ? qij : qij + qji;
+          double qe = (i == j) ? qij : qij + qji;
+          if constexpr (!init) qe += qp0[e * C];
+          qp0[e * C] = qe;
           ++e;
         }
       // psi_{j-1} = R beta, lambda_{j-1} = R conj(D) alpha
@@ -305,14 +332,15 @@ __global__ void __launch_bounds__(C * SC::TPC) __attribute__((amdgpu_waves_per_e
       }
     }
   };
-  if (nv >= 1) vact(iv0);
-  if (nv >= 2) vact(iv1);
+  if (nv >= 1) vact(iv0, std::bool_constant<EDGE == ADJ_SEED>{});
+  if constexpr (EDGE == ADJ_CKPT) fetch(0, ckpt);
+  if (nv >= 2) vact(iv1, std::false_type{});
   if constexpr (KZ) {
 #pragma unroll
-    for (int s = 0; s < P; ++s) fft_forward<SC, 1>(v + s, lds, lay, tw, t);
-    axis_phase<double, SC, P>(v, fz, -1.0, t);
+    for (int s = 0; s < P; s += S) fft_forward<SC, S>(v + s, lds, lay, tws, t);
+    axis_phase<double, SC, P>(v, tws + N, -1.0, t);
 #pragma unroll
-    for (int s = 0; s < P; ++s) fft_inverse<SC, 1>(v + s, lds, lay, tw, t);
+    for (int s = 0; s < P; s += S) fft_inverse<SC, S>(v + s, lds, lay, tws, t);
   }
 #pragma unroll
   for (int s = 0; s < P; ++s) {
@@ -849,11 +877,18 @@ struct Passes {
 
   template <bool KZ>
   static hipError_t za(const DevView& d, const AdjointView& a, int nv, int iv0, int iv1,
-                       int tidx) {
+                       int tidx, const double* w, const void* ckpt) {
+    if (w) return zae<KZ, ADJ_SEED>(d, a, nv, iv0, iv1, tidx, w, ckpt);
+    if (ckpt) return zae<KZ, ADJ_CKPT>(d, a, nv, iv0, iv1, tidx, w, ckpt);
+    return zae<KZ, ADJ_PLAIN>(d, a, nv, iv0, iv1, tidx, w, ckpt);
+  }
+  template <bool KZ, int EDGE>
+  static hipError_t zae(const DevView& d, const AdjointView& a, int nv, int iv0, int iv1,
+                        int tidx, const double* w, const void* ckpt) {
     using SA = typename AdjSched<SC>::type;
     constexpr int CA = kAdjCols;
-    auto k = k3d_zpass_adj<SA, S, CA, kTableCols, KZ>;
-    const size_t lds = (size_t)CA * N * sizeof(cx<double>);
+    auto k = k3d_zpass_adj<SA, S, CA, kTableCols, KZ, EDGE>;
+    const size_t lds = (size_t)(S * CA + 2) * N * sizeof(cx<double>);
     hipError_t e = set_lds(k, lds);
     if (e != hipSuccess) return e;
     // psi, lambda read + written; per action the eigen table (eig_slots(S)
@@ -861,20 +896,23 @@ struct Passes {
     // (S(S+1)/2 doubles, read + written)
     constexpr double NE = S * (S + 1) / 2.0;
     constexpr double NQ = S >= 2 ? eig_slots(S) : 1;
-    const double bytes = ((4.0 * S + nv * NQ) * sizeof(cx<double>) +
-                          nv * 2.0 * NE * sizeof(double)) * (double)d.npts;
+    // (seeding, lambda and the accumulator are not read; psi is read again
+    // from a checkpoint)
+    const double bytes = ((4.0 * S + nv * NQ + (ckpt ? S : 0) - (w ? S : 0)) * sizeof(cx<double>) +
+                          (nv * 2.0 - (w ? 1 : 0)) * NE * sizeof(double)) * (double)d.npts;
     TimedLaunch tl(d, KIND_OTHER, bytes);
     hipLaunchKernelGGL(k, dim3(N / CA, N), dim3(CA * SA::TPC), lds, d.stream,
                        (cx<double>*)a.stacked, (const cx<double>*)a.eig, a.qacc, a.taus, nv,
                        iv0, iv1,
                        (const cx<double>*)d.tw[0],
-                       KZ ? (const cx<double>*)kfac(d, tidx, 0) : nullptr);
+                       KZ ? (const cx<double>*)kfac(d, tidx, 0) : nullptr, w,
+                       (const cx<double>*)ckpt);
     return hipGetLastError();
   }
 
   // Backward sweep: steps nsteps..1, each step's actions in reverse order
   // with conjugated tables on [psi; lambda]; psi is replaced by the stored
-  // checkpoint at every step index that is a multiple of K.
+  // checkpoint at every inner step index that is a multiple of K.
   static hipError_t adjoint_backward(const DevView& d, const AdjointView& a, int64_t nsteps,
                                      int K) {
     if constexpr (!std::is_same<T, double>::value) {
@@ -885,13 +923,26 @@ struct Passes {
       cx<T>* stk = (cx<T>*)a.stacked;
       PassMachine m;
       std::vector<PassDesc> ps;
+      bool seeded = false;
+      const void* ckpt = nullptr;  // psi to take up after the next z-pass's first action
       auto run = [&]() -> hipError_t {
         for (const PassDesc& p : ps) {
-          hipError_t r;
+          hipError_t r = hipSuccess;
+          const double* w = nullptr;
+          if (!seeded) {
+            // the first z-pass seeds lambda and the accumulator if it holds an action
+            seeded = true;
+            if (p.kind == PassDesc::Z && p.nv > 0)
+              w = a.weights;
+            else
+              r = adjoint_seed(d, stk + (size_t)S * d.npts, stk, a.weights, a.qacc);
+            if (r != hipSuccess) return r;
+          }
           switch (p.kind) {
             case PassDesc::Z:
-              r = p.kz ? za<true>(d, a, p.nv, p.iv0, p.iv1, p.tidx)
-                       : za<false>(d, a, p.nv, p.iv0, p.iv1, 0);
+              r = p.kz ? za<true>(d, a, p.nv, p.iv0, p.iv1, p.tidx, w, ckpt)
+                       : za<false>(d, a, p.nv, p.iv0, p.iv1, 0, w, ckpt);
+              ckpt = nullptr;
               break;
             case PassDesc::Y: r = ypass(d2, stk, p.tidx, 1); break;
             default: r = xpass(d2, stk, p.tidx, 1); break;
@@ -904,17 +955,20 @@ struct Passes {
       hipError_t e = hipSuccess;
       for (int64_t n = nsteps; n >= 1; --n) {
         for (int i = d.nact - 1; i >= 0; --i) emit_action(m, d.hprog[i], ps, false);
-        if ((n - 1) % K == 0) {
-          emit_flush(m, ps);
-          if ((e = run()) != hipSuccess) return e;
-          const size_t bytes = (size_t)S * d.npts * sizeof(cx<T>);
-          e = hipMemcpyAsync(a.stacked, (const char*)a.checkpoints + (size_t)((n - 1) / K) * bytes,
-                             bytes, hipMemcpyDeviceToDevice, d.stream);
-          if (e != hipSuccess) return e;
-          if (d.timer) d.timer->break_chain();
-        } else if ((e = run()) != hipSuccess) {
-          return e;
+        if ((e = run()) != hipSuccess) return e;
+        if ((n - 1) % K != 0 || n == 1) continue;
+        const size_t bytes = (size_t)S * d.npts * sizeof(cx<T>);
+        const char* const at = (const char*)a.checkpoints + (size_t)((n - 1) / K) * bytes;
+        if (m.znv == 1) {  // the held action's z-pass takes psi up after it
+          ckpt = at;
+          continue;
         }
+        emit_flush(m, ps);
+        if ((e = run()) != hipSuccess) return e;
+        if ((e = hipMemcpyAsync(a.stacked, at, bytes, hipMemcpyDeviceToDevice, d.stream)) !=
+            hipSuccess)
+          return e;
+        if (d.timer) d.timer->break_chain();
       }
       emit_flush(m, ps);
       return run();

@@ -15,6 +15,8 @@
 // (the observables' sums with <T> are in kernels_1d.hip and kernels_3d.hip,
 // with the transforms they need); every sum is FP64 with a fixed block
 // count and a fixed-order tree, so results are bitwise reproducible.
+#include <algorithm>
+
 #include "fft_core.hpp"
 #include "internal.hpp"
 
@@ -392,16 +394,21 @@ __global__ void __launch_bounds__(256)
   }
 }
 
-// vraw = vbase + sum_k delta_k dv_k (the potential is linear in its parameters).
+// vraw = vbase + sum_k delta_k dv_k (the potential is linear in its parameters);
+// grid (blocks, packed entries).  Bound by its bytes: 128^3 x 3 with three
+// couplings, all entries of dv read 80 us, the nonzero ones 42 us.
 __global__ void __launch_bounds__(256)
     k_vparams(double* __restrict__ vraw, const double* __restrict__ vbase,
-              const double* __restrict__ dv, const double* __restrict__ delta, int nparams,
-              int64_t n) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    double v = vbase[i];
-    for (int k = 0; k < nparams; ++k) v += delta[k] * dv[(int64_t)k * n + i];
-    vraw[i] = v;
+              const double* __restrict__ dv, EntryMasks mask, const double* __restrict__ delta,
+              int nparams, int64_t npts) {
+  const int64_t e0 = (int64_t)blockIdx.y * npts;
+  const int64_t table = (int64_t)gridDim.y * npts;
+  for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < npts;
+       x += (int64_t)gridDim.x * blockDim.x) {
+    double v = vbase[e0 + x];
+    for (int k = 0; k < nparams; ++k)
+      if ((mask.m[k] >> blockIdx.y) & 1) v += delta[k] * dv[k * table + e0 + x];
+    vraw[e0 + x] = v;
   }
 }
 
@@ -424,11 +431,12 @@ __global__ void __launch_bounds__(256) k_zero(double* __restrict__ p, int64_t n)
 
 // Per block: g_k = sum_x sum_e Q_e(x) dv[k][e][x], k < NP, with Q_e(x) read
 // from the accumulator's tile layout [tile (y, x/C)][z][e][x % C] on an n^3
-// grid (point x = (z n + y) n + x0).
+// grid (point x = (z n + y) n + x0).  Bound by its bytes, of which the zero
+// entries of dv were most (128^3 x 3, three couplings: 102 -> 40 us).
 template <int NP>
 __global__ void __launch_bounds__(kReduceThreads)
-    k_grad_partials(const double* __restrict__ qacc, const double* __restrict__ dv, int NE,
-                    int64_t npts, int n, int cols, double* __restrict__ partials) {
+    k_grad_partials(const double* __restrict__ qacc, const double* __restrict__ dv,
+                    EntryMasks mask, int NE, int64_t npts, int n, int cols, double* __restrict__ partials) {
   double acc[NP];
 #pragma unroll
   for (int k = 0; k < NP; ++k) acc[k] = 0.0;
@@ -441,7 +449,8 @@ __global__ void __launch_bounds__(kReduceThreads)
     for (int e = 0; e < NE; ++e) {
       const double q = qacc[qb + (int64_t)e * cols];
 #pragma unroll
-      for (int k = 0; k < NP; ++k) acc[k] += q * dv[((int64_t)k * NE + e) * npts + x];
+      for (int k = 0; k < NP; ++k)
+        if ((mask.m[k] >> e) & 1) acc[k] += q * dv[((int64_t)k * NE + e) * npts + x];
     }
   }
   block_sum<NP>(acc, partials + (size_t)blockIdx.x * NP);
@@ -507,10 +516,10 @@ hipError_t form_eig(const DevView& d, const double* vraw_dev, int tile, void* ou
 }
 
 hipError_t set_vparams(const DevView& d, double* vraw, const double* vbase, const double* dv,
-                       const double* delta_dev, int nparams) {
-  const int64_t n = (int64_t)d.S * (d.S + 1) / 2 * d.npts;
-  hipLaunchKernelGGL(k_vparams, dim3(2048), dim3(256), 0, d.stream, vraw, vbase, dv, delta_dev,
-                     nparams, n);
+                       const EntryMasks& mask, const double* delta_dev, int nparams) {
+  const int blocks = (int)std::min<int64_t>(1024, (d.npts + 255) / 256);
+  hipLaunchKernelGGL(k_vparams, dim3(blocks, d.S * (d.S + 1) / 2), dim3(256), 0, d.stream, vraw,
+                     vbase, dv, mask, delta_dev, nparams, d.npts);
   return hipGetLastError();
 }
 
@@ -526,14 +535,19 @@ hipError_t adjoint_seed(const DevView& d, void* lam, const void* psi, const doub
 }
 
 hipError_t grad_reduce(const DevView& d, const double* qacc, int cols, const double* dv,
-                       int nparams, double* partials, double* out_dev) {
+                       const EntryMasks& nonzero, int nparams, double* partials,
+                       double* out_dev) {
   if (d.ndim != 3 || cols <= 0 || d.n[0] % cols != 0) return hipErrorInvalidValue;
   const int NE = d.S * (d.S + 1) / 2;
+  // a table of zeros keeps one entry, so that a sum over invalid (NaN) values
+  // is NaN for it too
+  EntryMasks mask = nonzero;
+  for (unsigned& m : mask.m) m |= m == 0;
   switch (nparams) {
 #define SOP_GRAD_CASE(K)                                                                    \
   case K:                                                                                   \
     hipLaunchKernelGGL(k_grad_partials<K>, dim3(kReduceBlocks), dim3(kReduceThreads), 0,    \
-                       d.stream, qacc, dv, NE, d.npts, d.n[0], cols, partials);             \
+                       d.stream, qacc, dv, mask, NE, d.npts, d.n[0], cols, partials);       \
     break;
     SOP_GRAD_CASE(1)
     SOP_GRAD_CASE(2)

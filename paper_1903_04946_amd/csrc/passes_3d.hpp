@@ -328,8 +328,8 @@ __device__ __forceinline__ void zpass_body(cx<T>* __restrict__ psi,
 // The z-pass with a potential action in eigen form on grids of 32, 48 and 64
 // points, for `ns` states of one plan: tile of C columns, NT threads.  The
 // action's work is spread over all threads by points (C N / NT each), handed
-// over in LDS, and the transforms are then one wave per surface (C * TPC = 64
-// threads), which needs no further barrier; each wave stores its pencils.
+// over in LDS, and the XX
+// (C * TPC threads), which needs no further barrier and stores its pencils.
 // R and the phases of a point are formed once for all states.
 // On these grids the z-pass is a chain of FP64 instructions, not traffic: with
 // eight (48: twelve) points and all surfaces in each of a wave's lanes

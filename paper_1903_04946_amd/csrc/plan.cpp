@@ -255,8 +255,9 @@ struct sop_plan {
   std::vector<double> theta;  // host copy of the current parameters
   double* d_drive = nullptr;  // drive samples of sop_propagate_driven
   size_t drive_cap = 0;       // doubles held by d_drive
-  unsigned dmask = 0;         // packed entries of dvtables[0] that are not zero everywhere
-  void* d_eig = nullptr;      // adjoint eigen table (FP64, tile layout)
+  sop::EntryMasks dmask;      // packed entries of each dvtables[k] that are not zero everywhere
+  bool adjoint = false;       // the plan serves the adjoint
+  void* d_eig = nullptr;      // its eigen table where d_vexp is not the eigen form
   double* d_w = nullptr;      // [S] adjoint weights
   sop::GraphCache* graphs = nullptr;
   bool use_graphs = true;
@@ -342,8 +343,9 @@ std::vector<ld> kinetic_factors(const sop_plan* p, const std::vector<double>& ta
 }
 
 // Largest Gershgorin row sum of a packed [S(S+1)/2][npts] symmetric table: a
-// bound on every |eigenvalue| at every point.
-double gershgorin_bound(const double* v, int S, int64_t npts) {
+// bound on every |eigenvalue| at every point.  `mask` (if given) receives the
+// entries that are not zero everywhere, bit e for entry e.
+double gershgorin_bound(const double* v, int S, int64_t npts, unsigned* mask = nullptr) {
   std::vector<int> idx((size_t)S * S);
   int e = 0;
   for (int i = 0; i < S; ++i)
@@ -365,6 +367,12 @@ double gershgorin_bound(const double* v, int S, int64_t npts) {
         for (int x = 0; x < m; ++x) row[x] += std::fabs(e0[x]);
       }
       for (int x = 0; x < m; ++x) best[x] = best[x] < row[x] ? row[x] : best[x];
+    }
+    for (int k = 0; mask && k < e; ++k) {
+      if ((*mask >> k) & 1) continue;
+      int any = 0;
+      for (int x = 0; x < m; ++x) any |= v[(int64_t)k * npts + x0 + x] != 0.0;  // NaN counts
+      if (any) *mask |= 1u << k;
     }
   }
   double b = 0.0;
@@ -409,6 +417,15 @@ hipError_t form_tables(sop_plan* p) {
   if (p->eig_form) return sop::form_eigq(p->dv, p->d_vraw, p->tile, p->d_vexp);
   return sop::form_vexp(p->dv, p->d_vraw, p->d_taus, (int)p->vtaus.size() + (p->vmid ? 1 : 0),
                         p->tile, p->d_vexp);
+}
+
+// The same after a change of V, with the adjoint's eigen table.  Where the
+// plan's own table is the eigen form, that one serves the adjoint too
+// (128^3 x 3: 46 us and 134 MB less than forming it twice).
+hipError_t form_new_v(sop_plan* p) {
+  const hipError_t e = form_tables(p);
+  if (e != hipSuccess || !p->d_eig) return e;
+  return sop::form_eig(p->dv, p->d_vraw, p->tile, p->d_eig);
 }
 
 // Rounds blocks of n interleaved extended-precision complex values to the
@@ -615,7 +632,8 @@ sop_status sop_plan_create_with_allocator(const sop_plan_desc* desc, void* hip_s
   if (sop::eig_form(p->ndim, S)) {
     p->vbound = gershgorin_bound(desc->vtable, S, p->npts);
     for (int k = 0; k < desc->nparams; ++k)
-      p->dvbound.push_back(gershgorin_bound(desc->dvtables + (size_t)k * NE * p->npts, S, p->npts));
+      p->dvbound.push_back(gershgorin_bound(desc->dvtables + (size_t)k * NE * p->npts, S, p->npts,
+                                            &p->dmask.m[k]));
     p->eig_form = phases_fit(p, p->vbound);
   }
   const size_t tbytes = p->eig_form ? (size_t)sop::eig_slots(S) * p->npts * 2 * sizeof(double)
@@ -718,8 +736,9 @@ sop_status sop_plan_create_with_allocator(const sop_plan_desc* desc, void* hip_s
     d.graphs = p->graphs;
   }
   p->nparams = desc->nparams;
-  // a driven run reads only the entries its one parameter table has
-  if (p->nparams == 1) p->dmask = entry_mask(desc->dvtables, NE, p->npts);
+  if (!sop::eig_form(p->ndim, S))
+    for (int k = 0; k < desc->nparams; ++k)
+      p->dmask.m[k] = entry_mask(desc->dvtables + (size_t)k * NE * p->npts, NE, p->npts);
   if (p->nparams > 0) {
     const size_t dvb = (size_t)p->nparams * vbytes;
     if (dalloc(p, &p->d_vbase, vbytes) != hipSuccess || dalloc(p, &p->d_dv, dvb) != hipSuccess ||
@@ -733,7 +752,8 @@ sop_status sop_plan_create_with_allocator(const sop_plan_desc* desc, void* hip_s
     p->theta.assign(p->nparams, 0.0);  // the V-table is V at theta = 0
     HIPTRY(hipMemcpyAsync(p->d_theta, p->theta.data(), p->nparams * sizeof(double),
                           hipMemcpyHostToDevice, stream));
-    if (p->ndim == 3 && f64 && sop::k3d_adjoint_supported(p->n[0], S, f64)) {
+    p->adjoint = p->ndim == 3 && f64 && sop::k3d_adjoint_supported(p->n[0], S, f64);
+    if (p->adjoint && !p->eig_form) {
       const int nslots = S >= 2 ? sop::eig_slots(S) : NE;  // compact eigen form for S >= 2
       if (dalloc(p, &p->d_eig, (size_t)nslots * p->npts * sizeof(double) * 2) != hipSuccess) {
         (void)hipGetLastError();
@@ -1373,9 +1393,9 @@ sop_status sop_plan_set_params(sop_plan* p, const double* theta) {
                 "these parameters take the phases tau*lambda beyond the eigen form's range");
   hipStream_t st = p->dv.stream;
   HIPTRY(hipMemcpyAsync(p->d_theta, theta, p->nparams * sizeof(double), hipMemcpyHostToDevice, st));
-  HIPTRY(sop::set_vparams(p->dv, p->d_vraw, p->d_vbase, p->d_dv, p->d_theta, p->nparams));
-  HIPTRY(form_tables(p));
-  if (p->d_eig) HIPTRY(sop::form_eig(p->dv, p->d_vraw, p->tile, p->d_eig));
+  HIPTRY(sop::set_vparams(p->dv, p->d_vraw, p->d_vbase, p->d_dv, p->dmask, p->d_theta,
+                          p->nparams));
+  HIPTRY(form_new_v(p));
   HIPTRY(hipStreamSynchronize(st));
   p->theta.assign(theta, theta + p->nparams);
   return SOP_OK;
@@ -1443,7 +1463,7 @@ sop_status sop_propagate_driven(sop_plan* p, void* psi, int64_t nsteps, const do
       (size_t)(p->S * (p->S + 1) / 2) * p->npts * p->csize * (p->dtype == SOP_C128 ? 1 : 2);
   // formation bytes per potential action: V0 and D's entries read, the table written
   const double fbytes =
-      ((p->S * (p->S + 1) / 2 + __builtin_popcount(p->dmask)) * (double)sizeof(double) +
+      ((p->S * (p->S + 1) / 2 + __builtin_popcount(p->dmask.m[0])) * (double)sizeof(double) +
        (p->eig_form ? sop::eig_slots(p->S) * 16.0 : (double)tab / (double)p->npts)) *
       (double)p->npts;
   const int nact = (int)p->dv.hprog.size();
@@ -1462,12 +1482,12 @@ sop_status sop_propagate_driven(sop_plan* p, void* psi, int64_t nsteps, const do
         const double* s_dev = p->d_drive + (size_t)n * nv + v++;
         sop::TimedLaunch tl(d, sop::KIND_OTHER, fbytes);
         if (p->eig_form) {
-          HIPTRY(sop::form_eigq(d, p->d_vbase, p->tile, p->d_vexp, p->d_dv, p->dmask,
+          HIPTRY(sop::form_eigq(d, p->d_vbase, p->tile, p->d_vexp, p->d_dv, p->dmask.m[0],
                                 s_dev));
         } else {  // only the table this action reads
           const int idx = code & 0xffff;
           HIPTRY(sop::form_vexp(d, p->d_vbase, p->d_taus + idx, 1, p->tile,
-                                (char*)p->d_vexp + (size_t)idx * tab, p->d_dv, p->dmask,
+                                (char*)p->d_vexp + (size_t)idx * tab, p->d_dv, p->dmask.m[0],
                                 s_dev));
         }
         if (a + 1 < nact && (p->dv.hprog[a + 1] >> 16) == sop::OP_T) na = 2;
@@ -1508,12 +1528,12 @@ sop_status sop_plan_update_v(sop_plan* p, const double* vtable) {
   const size_t vbytes = nv * sizeof(double);
   if (p->nparams > 0) {
     HIPTRY(hipMemcpyAsync(p->d_vbase, vtable, vbytes, hipMemcpyHostToDevice, st));
-    HIPTRY(sop::set_vparams(p->dv, p->d_vraw, p->d_vbase, p->d_dv, p->d_theta, p->nparams));
+    HIPTRY(sop::set_vparams(p->dv, p->d_vraw, p->d_vbase, p->d_dv, p->dmask, p->d_theta,
+                          p->nparams));
   } else {
     HIPTRY(hipMemcpyAsync(p->d_vraw, vtable, vbytes, hipMemcpyHostToDevice, st));
   }
-  HIPTRY(form_tables(p));
-  if (p->d_eig) HIPTRY(sop::form_eig(p->dv, p->d_vraw, p->tile, p->d_eig));
+  HIPTRY(form_new_v(p));
   HIPTRY(hipStreamSynchronize(st));
   if (p->eig_form) p->vbound = vb;
   return SOP_OK;
@@ -1530,7 +1550,7 @@ sop_status adjoint_check(const sop_plan* p, int64_t nsteps, int K, AdjLayout* la
   if (!p) return fail(SOP_ERR_INVALID, "plan is NULL");
   if (nsteps < 1 || K < 1) return fail(SOP_ERR_INVALID, "nsteps and K must be >= 1");
   if (p->nparams == 0) return fail(SOP_ERR_STATE, "plan has no parameters (nparams = 0)");
-  if (!p->d_eig) return fail(SOP_ERR_UNSUPPORTED, "the adjoint needs an FP64 3D plan with n in {32, 64, 128, 256}");
+  if (!p->adjoint) return fail(SOP_ERR_UNSUPPORTED, "the adjoint needs an FP64 3D plan with n in {32, 64, 128, 256}");
   const size_t sb = (size_t)p->S * p->npts * sizeof(double) * 2;
   lay->ncp = (nsteps + K - 1) / K;
   lay->psi = 0;                                   // psi then lambda: 2 * sb
@@ -1587,18 +1607,17 @@ sop_status sop_adjoint_backward(sop_plan* p, int64_t nsteps, int K, const double
     if (!std::isfinite(weights[q])) return fail(SOP_ERR_INVALID, "weights must be finite");
   hipStream_t s = p->dv.stream;
   char* w = (char*)ws;
-  const size_t sb = (size_t)p->S * p->npts * sizeof(double) * 2;
   HIPTRY(hipMemcpyAsync(p->d_w, weights, p->S * sizeof(double), hipMemcpyHostToDevice, s));
-  HIPTRY(sop::adjoint_seed(p->dv, w + lay.psi + sb, w + lay.psi, p->d_w, (double*)(w + lay.qacc)));
   sop::AdjointView a;
   a.stacked = w + lay.psi;
-  a.eig = p->d_eig;
+  a.eig = p->eig_form ? p->d_vexp : p->d_eig;
   a.qacc = (double*)(w + lay.qacc);
   a.taus = p->d_taus;
+  a.weights = p->d_w;
   a.checkpoints = w + lay.ckpt;
   HIPTRY(sop::k3d_adjoint_backward(p->dv, a, nsteps, K));
-  HIPTRY(sop::grad_reduce(p->dv, a.qacc, sop::k3d_adjoint_cols(p->n[0]), p->d_dv, p->nparams,
-                          p->d_part, p->d_out));
+  HIPTRY(sop::grad_reduce(p->dv, a.qacc, sop::k3d_adjoint_cols(p->n[0]), p->d_dv, p->dmask,
+                          p->nparams, p->d_part, p->d_out));
   double raw[sop::kMaxParams];
   HIPTRY(hipMemcpyAsync(raw, p->d_out, p->nparams * sizeof(double), hipMemcpyDeviceToHost, s));
   HIPTRY(hipStreamSynchronize(s));
