@@ -94,6 +94,16 @@ struct GraphCache {
   }
 };
 
+// V = V0 + *s D, formed inside the z-pass (packed entries; mask: those of D
+// that are not zero everywhere)
+constexpr int kDrivenZMax = 128;  // longest axis of it
+struct DrivenV {
+  const double* v0 = nullptr;
+  const double* d = nullptr;
+  unsigned mask = 0;
+  const double* s = nullptr;
+};
+
 // Device-side view of a plan that the launchers need.
 struct DevView {
   int ndim = 1;
@@ -117,6 +127,8 @@ struct DevView {
   // the first of the next, where both are kinetic (TVT) or, on 1D grids, both
   // potential (VTV), as one action with the summed coefficient; -1: none
   int mid = -1;
+  // 3D eigen form: a driven action forms its V in the z-pass (v0 set)
+  DrivenV driven;
   // 1D: device list of a run with merged boundaries: the program with `mid`
   // before its last action
   const int* prog_mid = nullptr;

@@ -104,6 +104,24 @@ struct ZTile<Z64> {
 // 256 threads: twice as many (fewer points each) cost more in barriers than
 // they hide (32^3 x 48 FP32: 23 -> 29 us; 48^3: 6.6 -> 7.5 us; 64^3: the same).
 constexpr int kZTileThreads = 256;
+// One action of V0 + s D (grids of up to 128 points, one state): its eigen form
+// is formed in the pass from the packed entries.  Against a table written by a
+// pass of its own (80 us at 128^3 x 3) and read back by the z-pass (57 us), and
+// the plan's table formed again at the end of the call, it saves 250 MB an
+// action: 109-120 us.  Bound by the Jacobi rotations' FP64 chains, for which
+// the tile's points are spread over its threads; with the points of a pencil
+// in each thread (zpass_body) the registers leave one wave a SIMD (144 us).
+// One call of 10 actions, 128^3 x 3: 2020 -> 1590-1690 us, 128^3 x 2: 1100 -> 1000
+// us; 64^3 x 3, 4 steps: 1530 -> 1150 us; 32^3 x 3: 640 -> 466 us.
+template <typename T, class SC, int S, int C, int NT, int AX>
+__global__ void __launch_bounds__(NT)
+    k3d_zdriven(cx<T>* __restrict__ psi, DrivenV drv, int iv0, const cx<T>* __restrict__ tw,
+                const cx<T>* __restrict__ fz, const double* __restrict__ taus) {
+  extern __shared__ char smem_raw[];
+  ztile_body<T, SC, S, C, NT, AX, true>(psi, 1, nullptr, taus[iv0], 0, tw, fz,
+                                        reinterpret_cast<cx<T>*>(smem_raw), blockIdx.x,
+                                        blockIdx.y, nullptr, drv);
+}
 template <typename T, class SC, int S, int C, int NT>
 __global__ void __launch_bounds__(NT)
     k3d_ztile(cx<T>* __restrict__ psi, int states, int per, const cx<double>* __restrict__ eig,
@@ -611,6 +629,9 @@ struct Passes {
   // the potential may come from the compact eigen form (one table for every
   // coefficient; plans whose phases stay within kPhaseMax)
   static constexpr bool EQ = eig_form(3, S);
+  // driven actions form V in the z-pass; a 256-point pencil's tile of whole
+  // waves would have 4 columns (64-byte pieces)
+  static constexpr bool DRIVEN = EQ && N <= kDrivenZMax;
 
   // algorithmic bytes of one pass: psi read + written (d.S pencil sets: the
   // adjoint's y- and x-passes run on the stacked 2S), plus tables read (the
@@ -631,12 +652,34 @@ struct Passes {
   static hipError_t z(const DevView& d, cx<T>* psi, int nv, int iv0, int iv1, int tidx,
                       int conj, const cx<T>* src = nullptr) {
     if constexpr (EQ) {
+      if (d.driven.v0 && nv == 1) return zdriven<AX>(d, psi, iv0, tidx);
       if constexpr (AX == AX_KIN && ZTile<SC>::C > 0) {
         if (d.eig && nv > 0) return ztile(d, psi, nv, iv0, iv1, tidx, conj, src);
       }
       if (d.eig) return zk<AX, true>(d, psi, nv, iv0, iv1, tidx, conj, src);
     }
     return zk<AX, false>(d, psi, nv, iv0, iv1, tidx, conj, src);
+  }
+  template <int AX>
+  static hipError_t zdriven(const DevView& d, cx<T>* psi, int iv0, int tidx) {
+    if constexpr (DRIVEN) {
+      // 128 points: 8 columns of 8 threads, so that a wave holds a surface's
+      // pencils; with two surfaces those are all of 128 threads (256: 3% more)
+      constexpr int CT = N == 128 ? 8 : ZTile<SC>::few;
+      constexpr int NT = N == 128 && S == 2 ? 128 : kZTileThreads;
+      auto k = k3d_zdriven<T, XS, S, CT, NT, AX>;
+      const size_t lds = AX == AX_KIN ? (size_t)S * CT * N * sizeof(cx<T>) : 0;
+      const hipError_t e = set_lds(k, lds);
+      if (e != hipSuccess) return e;
+      const int entries = S * (S + 1) / 2 + __builtin_popcount(d.driven.mask);
+      TimedLaunch tl(d, KIND_ZPASS, pass_bytes(d, 0) + entries * 8.0 * (double)d.npts);
+      hipLaunchKernelGGL(k, dim3(N / CT, N), dim3(NT), lds, d.stream, psi, d.driven, iv0,
+                         (const cx<T>*)d.tw[0], AX == AX_KIN ? kfac(d, tidx, 0) : nullptr,
+                         d.vtaus);
+      return hipGetLastError();
+    } else {
+      return hipErrorInvalidValue;
+    }
   }
   static hipError_t ztile(const DevView& d, cx<T>* psi, int nv, int iv0, int iv1, int tidx,
                           int conj, const cx<T>* src) {

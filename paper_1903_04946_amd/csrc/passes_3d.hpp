@@ -22,6 +22,7 @@
 // carries the 1/n_d of the unnormalised inverse transform.
 #pragma once
 
+#include "eigen.hpp"
 #include "fft_core.hpp"
 #include "internal.hpp"
 
@@ -228,6 +229,42 @@ struct EigPoint {
   }
 };
 
+// The packed entries of V0 + s D at points of one grid (the entries of D that
+// are zero everywhere, clear in mask, come from descriptors of no extent).
+template <int S>
+struct DrivenRead {
+  static constexpr int NE = S * (S + 1) / 2;
+  const DrivenV& d;
+  int64_t npts;
+  double s;
+  __device__ __forceinline__ void load(double (&v0)[NE], double (&v1)[NE], uint32_t pt) const {
+    const uint32_t bytes = (uint32_t)npts * 8u;
+#pragma unroll
+    for (int e = 0; e < NE; ++e) {
+      const auto r0 = __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(d.v0 + e * npts),
+                                                        (short)0, (int)bytes, 0x00020000);
+      const auto r1 = __builtin_amdgcn_make_buffer_rsrc(
+          const_cast<double*>(d.d + e * npts), (short)0, (d.mask >> e) & 1 ? (int)bytes : 0,
+          0x00020000);
+      v0[e] = __builtin_bit_cast(
+          double, __builtin_amdgcn_raw_buffer_load_b64(r0, (int)(pt * 8u), 0, 0));
+      v1[e] = __builtin_bit_cast(
+          double, __builtin_amdgcn_raw_buffer_load_b64(r1, (int)(pt * 8u), 0, 0));
+    }
+  }
+  __device__ __forceinline__ void slots(const double (&v0)[NE], const double (&v1)[NE],
+                                        cx<double> (&sl)[eig_slots(S)]) const {
+    double A[S][S], R[S][S];
+    int e = 0;
+#pragma unroll
+    for (int i = 0; i < S; ++i)
+#pragma unroll
+      for (int j = i; j < S; ++j, ++e) A[i][j] = A[j][i] = v0[e] + s * v1[e];
+    jacobi_sym<S>(A, R);
+    eig_form_slots<S>(A, R, sl);
+  }
+};
+
 template <typename T, class SC, int S, int C, int TC, int AX, bool EQ = false>
 __device__ __forceinline__ void zpass_body(cx<T>* __restrict__ psi,
                                            const void* __restrict__ vexp, int nv, int iv0,
@@ -328,7 +365,7 @@ __device__ __forceinline__ void zpass_body(cx<T>* __restrict__ psi,
 // The z-pass with a potential action in eigen form on grids of 32, 48 and 64
 // points, for `ns` states of one plan: tile of C columns, NT threads.  The
 // action's work is spread over all threads by points (C N / NT each), handed
-// over in LDS, and the XX
+// over in LDS, and the transforms are then a wave or half of one per surface
 // (C * TPC threads), which needs no further barrier and stores its pencils.
 // R and the phases of a point are formed once for all states.
 // On these grids the z-pass is a chain of FP64 instructions, not traffic: with
@@ -338,12 +375,12 @@ __device__ __forceinline__ void zpass_body(cx<T>* __restrict__ psi,
 // state, zpass_body -> now: 32^3 x 3: 8.4 -> 4.5, 48^3 x 2: 9.9 -> 6.6, 64^3 x
 // 3: 13.2 -> 9.8.  From 128 points on the pass is bound by memory: zpass_body.
 // The same operations as zpass_body (EQ, AX_KIN) in the same order.
-template <typename T, class SC, int S, int C, int NT>
+template <typename T, class SC, int S, int C, int NT, int AX = AX_KIN, bool DRV = false>
 __device__ __forceinline__ void ztile_body(cx<T>* __restrict__ psi, int ns,
                                            const cx<double>* __restrict__ eig, double tau,
                                            int conj, const cx<T>* __restrict__ tw,
                                            const cx<T>* __restrict__ fz, cx<T>* lds, int bx,
-                                           int by, const cx<T>* src) {
+                                           int by, const cx<T>* src, const DrivenV& drv = {}) {
   constexpr int N = SC::N, E = SC::E, NE = eig_slots(S), TC = s3d::kTableCols;
   constexpr int FT = C * SC::TPC;  // threads of one surface's transforms
   static_assert(64 % FT == 0 && NT >= FT * S && (C * N) % NT == 0 && TC % C == 0, "tile");
@@ -356,13 +393,20 @@ __device__ __forceinline__ void ztile_body(cx<T>* __restrict__ psi, int ns,
   const size_t tbase = ((size_t)by * (N / TC) + (bx * C) / TC) * tile;
   const int tcol = (bx * C) % TC + lane % C;
   const T csign = conj ? (T)-1 : (T)1;
-  const auto rq = rsrc(eig + tbase, tile);
   cx<double> sl[PP][NE];
+  [[maybe_unused]] const DrivenRead<S> dr{drv, npts, DRV ? *drv.s : 0.0};
+  [[maybe_unused]] double a0[PP][S * (S + 1) / 2], a1[PP][S * (S + 1) / 2];
 #pragma unroll
-  for (int i = 0; i < PP; ++i)
+  for (int i = 0; i < PP; ++i) {
+    const uint32_t z = lane / C + i * (NT / C);
+    if constexpr (DRV) {
+      dr.load(a0[i], a1[i], z * plane + off0 + lane % C);
+    } else {
+      const auto rq = rsrc(eig + tbase, tile);
 #pragma unroll
-    for (int e = 0; e < NE; ++e)
-      sl[i][e] = ld<double>(rq, (uint32_t)(((lane / C + i * (NT / C)) * NE + e) * TC + tcol));
+      for (int e = 0; e < NE; ++e) sl[i][e] = ld<double>(rq, (z * NE + e) * TC + tcol);
+    }
+  }
   cx<T> w[PP][S];
   auto fetch = [&](int m) {  // the thread's points of state m
 #pragma unroll
@@ -377,10 +421,25 @@ __device__ __forceinline__ void ztile_body(cx<T>* __restrict__ psi, int ns,
   const int wv = lane / FT, l = lane % FT, col = l % C, t = l / C;
   EigPoint<S> ep[PP];
 #pragma unroll
-  for (int i = 0; i < PP; ++i) ep[i].form(sl[i], (double)csign * tau);
+  for (int i = 0; i < PP; ++i) {
+    if constexpr (DRV) dr.slots(a0[i], a1[i], sl[i]);
+    ep[i].form(sl[i], (double)csign * tau);
+  }
   for (int m = 0; m < ns; ++m) {
     cx<T>* const out = psi + (size_t)m * S * npts;
     if (m > 0) fetch(m);
+    if constexpr (AX == AX_NONE) {
+#pragma unroll
+      for (int i = 0; i < PP; ++i) ep[i].apply(w[i]);
+#pragma unroll
+      for (int s = 0; s < S; ++s) {
+        const auto rs = rsrc(out + s * npts, (uint32_t)npts);
+#pragma unroll
+        for (int i = 0; i < PP; ++i)
+          st(rs, (uint32_t)(lane / C + i * (NT / C)) * plane + off0 + lane % C, w[i][s]);
+      }
+      continue;
+    }
     if (m > 0) __syncthreads();  // the previous state's transforms are done with LDS
 #pragma unroll
     for (int i = 0; i < PP; ++i) {

@@ -1467,6 +1467,9 @@ sop_status sop_propagate_driven(sop_plan* p, void* psi, int64_t nsteps, const do
        (p->eig_form ? sop::eig_slots(p->S) * 16.0 : (double)tab / (double)p->npts)) *
       (double)p->npts;
   const int nact = (int)p->dv.hprog.size();
+  // 3D eigen form up to 128 points: V0 + s D is formed inside the z-pass, and
+  // the plan's table stays as it is
+  const bool fused = p->eig_form && p->n[0] <= sop::kDrivenZMax;
   const sop_status run = [&]() -> sop_status {
   for (int64_t n = 0; n < nsteps; ++n) {
     int v = 0;
@@ -1478,10 +1481,13 @@ sop_status sop_propagate_driven(sop_plan* p, void* psi, int64_t nsteps, const do
       // alone
       int na = 1;
       if ((code >> 16) == sop::OP_V) {
-        // V = V0 + s D formed inside the table kernel (no V table written)
+        // V = V0 + s D formed inside the z-pass or the table kernel (no V table
+        // written)
         const double* s_dev = p->d_drive + (size_t)n * nv + v++;
-        sop::TimedLaunch tl(d, sop::KIND_OTHER, fbytes);
-        if (p->eig_form) {
+        d.driven = {};
+        if (fused) {
+          d.driven = {p->d_vbase, p->d_dv, p->dmask.m[0], s_dev};
+        } else if (sop::TimedLaunch tl(d, sop::KIND_OTHER, fbytes); p->eig_form) {
           HIPTRY(sop::form_eigq(d, p->d_vbase, p->tile, p->d_vexp, p->d_dv, p->dmask.m[0],
                                 s_dev));
         } else {  // only the table this action reads
@@ -1506,7 +1512,7 @@ sop_status sop_propagate_driven(sop_plan* p, void* psi, int64_t nsteps, const do
   }();
   // back to the tables of the plan's own V (its V-table was not touched), on
   // every exit path: a failed action must not leave the driven tables behind
-  const hipError_t ef = form_tables(p);
+  const hipError_t ef = fused ? hipSuccess : form_tables(p);
   const hipError_t es = hipStreamSynchronize(st);
   if (run != SOP_OK) return run;  // the loop's failure text is kept
   HIPTRY(ef);
