@@ -316,17 +316,20 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const cx<T>* p, uint32_t 
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<cx<T>*>(p), (short)0,
                                            (int)(nelem * (uint32_t)sizeof(cx<T>)), 0x00020000);
 }
+// CPOL: cache-policy bits (0, or 2 for non-temporal)
+template <int CPOL = 0>
 __device__ __forceinline__ cx<double> bld(__amdgpu_buffer_rsrc_t r, uint32_t idx, cx<double>*) {
-  sop_u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)(idx * 16u), 0, 0);
+  sop_u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)(idx * 16u), 0, CPOL);
   return __builtin_bit_cast(cx<double>, v);
 }
+template <int CPOL = 0>
 __device__ __forceinline__ cx<float> bld(__amdgpu_buffer_rsrc_t r, uint32_t idx, cx<float>*) {
-  sop_u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(r, (int)(idx * 8u), 0, 0);
+  sop_u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(r, (int)(idx * 8u), 0, CPOL);
   return __builtin_bit_cast(cx<float>, v);
 }
-template <typename T>
+template <typename T, int CPOL = 0>
 __device__ __forceinline__ cx<T> ld(__amdgpu_buffer_rsrc_t r, uint32_t idx) {
-  return bld(r, idx, (cx<T>*)nullptr);
+  return bld<CPOL>(r, idx, (cx<T>*)nullptr);
 }
 // Entry idx of a factor table (Split<T>::rep complex values per entry: in
 // FP32 the pair (rounded, residue), 16 bytes read by one load), conjugated
@@ -360,11 +363,15 @@ __device__ __forceinline__ Fac<T> ldfac_at(__amdgpu_buffer_rsrc_t r, uint32_t of
   }
   return F;
 }
+template <int CPOL = 0>
 __device__ __forceinline__ void st(__amdgpu_buffer_rsrc_t r, uint32_t idx, cx<double> v) {
-  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(sop_u32x4, v), r, (int)(idx * 16u), 0, 0);
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(sop_u32x4, v), r, (int)(idx * 16u), 0,
+                                         CPOL);
 }
+template <int CPOL = 0>
 __device__ __forceinline__ void st(__amdgpu_buffer_rsrc_t r, uint32_t idx, cx<float> v) {
-  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(sop_u32x2, v), r, (int)(idx * 8u), 0, 0);
+  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(sop_u32x2, v), r, (int)(idx * 8u), 0,
+                                        CPOL);
 }
 
 // The thread index passed through an empty asm statement: the compiler can no

@@ -265,6 +265,15 @@ struct DrivenRead {
   }
 };
 
+// On FP64 grids of 256 points a surface fills the last-level cache (268 MB) and
+// little of the z-pass's output is left there for the y-pass: the z-pass stores
+// and the y-pass loads it with the non-temporal hint, which spares the y-pass
+// the write-back of what it evicts (256^3 x 3: y 308 -> 281 us a pass, 292 with
+// the stores alone; z and x the same.  On the z-pass's loads, and on the y- and
+// x-passes' stores and the x-pass's loads, it gains nothing).
+template <typename T, int N>
+constexpr int kStateCpol = N >= 256 && sizeof(T) == 8 ? kCpolNT : 0;
+
 template <typename T, class SC, int S, int C, int TC, int AX, bool EQ = false>
 __device__ __forceinline__ void zpass_body(cx<T>* __restrict__ psi,
                                            const void* __restrict__ vexp, int nv, int iv0,
@@ -357,7 +366,8 @@ __device__ __forceinline__ void zpass_body(cx<T>* __restrict__ psi,
   for (int s = 0; s < S; ++s) {
     const auto rs = rsrc(psi + s * npts, (uint32_t)npts);
 #pragma unroll
-    for (int q = 0; q < E; ++q) st(rs, own_idx<N, E, SC::RF>(t, q) * plane + off0, v[s][q]);
+    for (int q = 0; q < E; ++q)
+      st<kStateCpol<T, N>>(rs, own_idx<N, E, SC::RF>(t, q) * plane + off0, v[s][q]);
   }
 }
 
@@ -486,7 +496,8 @@ __device__ __forceinline__ void ypass_body(cx<T>* __restrict__ psi_s,
   stage_blocks<T, N, 2>(tws, {tw, fy}, lane, C * SC::TPC);
   cx<T> v[1][E];
 #pragma unroll
-  for (int q = 0; q < E; ++q) v[0][q] = ld<T>(bin, own_idx<N, E, SC::RF>(t, q) * N + x);
+  for (int q = 0; q < E; ++q)
+    v[0][q] = ld<T, kStateCpol<T, N>>(bin, own_idx<N, E, SC::RF>(t, q) * N + x);
   fft_forward<SC, 1>(v, lds, lay, tws, t);
   axis_phase<T, SC, 1>(v, tws + axis_block<T, N>(), conj ? (T)-1 : (T)1, t);
   fft_inverse<SC, 1>(v, lds, lay, tws, t);
