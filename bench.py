@@ -721,7 +721,7 @@ def run_interp(a, torch, soprop):
         "data": "synthetic",
         "config": {"workload": a.workload, "ndim": 3, "grid_src": [na] * 3, "grid_dst": [nb] * 3,
                    "box_src": [-7.0, 7.0], "box_dst": [-7.0 * r2, 7.0 * r2], "nsurf": ma.nsurf},
-        "roofline": {"bound": "alu", "kernel": "interp (complex FP64 products, three per call)",
+        "roofline": {"bound": "alu", "kernel": "interp (FP64 matrix-core products, three per call)",
                      "achieved": achieved, "peak": FP64_PEAK_TFS, "unit": "TFLOP/s",
                      "frac": achieved / FP64_PEAK_TFS, "traffic": None,
                      "flops_per_call": flops_call, "call_TFLOPs": tflops},

@@ -371,14 +371,14 @@ __global__ void __launch_bounds__(C * SC::TPC) __attribute__((amdgpu_waves_per_e
 // ---------------------------------------------------------------- y-pass
 // grid (N / C, N, surfaces x states): blockIdx.z picks one surface pencil set;
 // fy = the y factor of the kinetic set
-template <typename T, class SC, int C>
+template <typename T, class SC, int C, int CPOL>
 __global__ void __launch_bounds__(C * SC::TPC)
     k3d_ypass(cx<T>* __restrict__ psi, const cx<T>* __restrict__ tw,
               const cx<T>* __restrict__ fy, int conj, const cx<T>* src) {
   extern __shared__ char smem_raw[];
   cx<T>* lds = reinterpret_cast<cx<T>*>(smem_raw);
   constexpr int64_t npts = (int64_t)SC::N * SC::N * SC::N;
-  ypass_body<T, SC, C>(psi + blockIdx.z * npts, tw, fy, conj, lds, blockIdx.x, blockIdx.y,
+  ypass_body<T, SC, C, CPOL>(psi + blockIdx.z * npts, tw, fy, conj, lds, blockIdx.x, blockIdx.y,
                            (int)threadIdx.x, src ? src + blockIdx.z * npts : nullptr);
 }
 
@@ -725,7 +725,7 @@ struct Passes {
   }
   static hipError_t ypass(const DevView& d, cx<T>* psi, int tidx, int conj,
                           const cx<T>* src = nullptr) {
-    auto k = k3d_ypass<T, XS, C>;
+    auto k = k3d_ypass<T, XS, C, kStateCpol<T, N, S>>;
     const size_t lds = y_lds_elems<T, N>(C) * sizeof(cx<T>);
     hipError_t e = set_lds(k, lds);
     if (e != hipSuccess) return e;

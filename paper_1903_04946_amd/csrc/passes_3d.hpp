@@ -265,14 +265,16 @@ struct DrivenRead {
   }
 };
 
-// On FP64 grids of 256 points a surface fills the last-level cache (268 MB) and
-// little of the z-pass's output is left there for the y-pass: the z-pass stores
-// and the y-pass loads it with the non-temporal hint, which spares the y-pass
-// the write-back of what it evicts (256^3 x 3: y 308 -> 281 us a pass, 292 with
-// the stores alone; z and x the same.  On the z-pass's loads, and on the y- and
-// x-passes' stores and the x-pass's loads, it gains nothing).
-template <typename T, int N>
-constexpr int kStateCpol = N >= 256 && sizeof(T) == 8 ? kCpolNT : 0;
+// On FP64 grids of 256 points a state of two or three surfaces (537, 805 MB) is
+// beyond the last-level cache (256 MB), and little of the z-pass's output is
+// left there for the y-pass: the z-pass stores and the y-pass loads it with the
+// non-temporal hint, which spares the y-pass the write-back of what it evicts
+// (256^3 x 3: y 308 -> 281 us a pass, 292 with the stores alone; z and x the
+// same.  On the z-pass's loads, and on the y- and x-passes' stores and the
+// x-pass's loads, it gains nothing).  One surface (268 MB) partly stays, and
+// loses with the hint (3.06 -> 3.14 ms a TJ-6 step).
+template <typename T, int N, int S>
+constexpr int kStateCpol = N >= 256 && S >= 2 && sizeof(T) == 8 ? kCpolNT : 0;
 
 template <typename T, class SC, int S, int C, int TC, int AX, bool EQ = false>
 __device__ __forceinline__ void zpass_body(cx<T>* __restrict__ psi,
@@ -367,7 +369,7 @@ __device__ __forceinline__ void zpass_body(cx<T>* __restrict__ psi,
     const auto rs = rsrc(psi + s * npts, (uint32_t)npts);
 #pragma unroll
     for (int q = 0; q < E; ++q)
-      st<kStateCpol<T, N>>(rs, own_idx<N, E, SC::RF>(t, q) * plane + off0, v[s][q]);
+      st<kStateCpol<T, N, S>>(rs, own_idx<N, E, SC::RF>(t, q) * plane + off0, v[s][q]);
   }
 }
 
@@ -478,8 +480,8 @@ __device__ __forceinline__ void ztile_body(cx<T>* __restrict__ psi, int ns,
 
 // ---------------------------------------------------------------- y-pass
 // One surface `psi_s` [N^3]; block (bx, z) owns columns bx*C .. bx*C+C-1 of
-// plane z; fy = the y factor.
-template <typename T, class SC, int C>
+// plane z; fy = the y factor; CPOL = cache-policy bits of the loads.
+template <typename T, class SC, int C, int CPOL = 0>
 __device__ __forceinline__ void ypass_body(cx<T>* __restrict__ psi_s,
                                            const cx<T>* __restrict__ tw,
                                            const cx<T>* __restrict__ fy, int conj, cx<T>* lds,
@@ -497,7 +499,7 @@ __device__ __forceinline__ void ypass_body(cx<T>* __restrict__ psi_s,
   cx<T> v[1][E];
 #pragma unroll
   for (int q = 0; q < E; ++q)
-    v[0][q] = ld<T, kStateCpol<T, N>>(bin, own_idx<N, E, SC::RF>(t, q) * N + x);
+    v[0][q] = ld<T, CPOL>(bin, own_idx<N, E, SC::RF>(t, q) * N + x);
   fft_forward<SC, 1>(v, lds, lay, tws, t);
   axis_phase<T, SC, 1>(v, tws + axis_block<T, N>(), conj ? (T)-1 : (T)1, t);
   fft_inverse<SC, 1>(v, lds, lay, tws, t);

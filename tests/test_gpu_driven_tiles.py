@@ -28,9 +28,9 @@ def torch_cuda():
     return torch
 
 
-@pytest.mark.parametrize("n", [32, 48, 64, 128, 256])
+@pytest.mark.parametrize("n,c64", [(n, c) for n in (32, 48, 64, 128) for c in (False, True)]
+                         + [(256, False)])
 @pytest.mark.parametrize("S", [2, 3])
-@pytest.mark.parametrize("c64", [False, True])
 def test_piecewise_constant_drive(torch_cuda, n, S, c64):
     """A drive constant over each step against static plans of V + s D, one
     step each (their tables come from the table kernel), to 1e-12 (FP64) and
@@ -38,8 +38,6 @@ def test_piecewise_constant_drive(torch_cuda, n, S, c64):
     untouched afterwards."""
     torch = torch_cuda
     from paper_1903_04946_amd import soprop
-    if n == 256 and c64:
-        pytest.skip("covered by the FP64 case: the same table path")
     m = synth.random_small([n] * 3, S, seed=n + S)
     dtype = torch.complex64 if c64 else torch.complex128
     tol = 5e-6 if c64 else 1e-12
