@@ -87,6 +87,8 @@ KERNEL_SOURCES = ["paper_1903_04946_amd/csrc/kernels_3d.hip",
                   "paper_1903_04946_amd/csrc/passes_3d.hpp",
                   "paper_1903_04946_amd/csrc/kernels_1d.hip",
                   "paper_1903_04946_amd/csrc/body_1d.hpp",
+                  "paper_1903_04946_amd/csrc/body_1d_waves.hpp",
+                  "paper_1903_04946_amd/csrc/eigen.hpp",
                   "paper_1903_04946_amd/csrc/fft_core.hpp"]
 
 
@@ -94,6 +96,7 @@ KERNEL_SOURCES = ["paper_1903_04946_amd/csrc/kernels_3d.hip",
 # summary stay valid while these are unchanged)
 PASS3D_SOURCES = ["paper_1903_04946_amd/csrc/kernels_3d.hip",
                   "paper_1903_04946_amd/csrc/passes_3d.hpp",
+                  "paper_1903_04946_amd/csrc/eigen.hpp",
                   "paper_1903_04946_amd/csrc/fft_core.hpp"]
 
 
