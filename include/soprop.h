@@ -417,7 +417,8 @@ sop_status sop_propagate_trapezoid_noalloc(sop_plan* plan, void* psi, int count,
  * receive zero.  Equal grids give psi_dst = psi_src up to rounding.
  * Both plans need the same ndim and nsurf and SOP_C128 (SOP_ERR_UNSUPPORTED
  * otherwise); their lengths and boxes may differ freely (destination axes up
- * to 65535 points).  psi_src and psi_dst are device buffers and must differ.
+ * to 65535 points).  psi_src and psi_dst are device buffers and must differ;
+ * on 3D grids they may overlap (psi_dst is written after psi_src was read).
  * Runs asynchronously on dst's stream (psi_src must be ready there); the
  * axis matrices and intermediate states live in a workspace that dst keeps
  * and grows on demand (8 bytes per matrix entry, 16 per intermediate
