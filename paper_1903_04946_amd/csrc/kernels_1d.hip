@@ -135,6 +135,8 @@ hipError_t launch_obs(const DevView& d, const void* psi, const double* vraw, dou
   auto k = k1d_obs_kernel<T, SC, S>;
   const hipError_t e = set_lds((const void*)k, one);
   if (e != hipSuccess) return e;
+  TimedLaunch tl(d, KIND_OTHER,
+                 S * SC::N * (sizeof(cx<T>) + (S + 1) / 2.0 * sizeof(double)));
   hipLaunchKernelGGL(k, dim3(1), dim3(SC::TPC), one, d.stream, (const cx<T>*)psi, vraw,
                      (const cx<T>*)d.tw[0], ck, out);
   return hipGetLastError();
@@ -191,6 +193,7 @@ hipError_t k1d_propagate(const DevView& d, void* psi, int64_t nsteps, int conj, 
 
 hipError_t k1d_observe(const DevView& d, const void* psi, const double* vraw, double ck,
                        double* out) {
+  if (d.timer) d.timer->break_chain();  // untimed work may precede this call
   return dispatch(d.n[0], d.S, d.f64, [&]<typename T, class SC, int S>() {
     return launch_obs<T, SC, S>(d, psi, vraw, ck, out);
   });

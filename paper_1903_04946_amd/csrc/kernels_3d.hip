@@ -879,11 +879,15 @@ struct Passes {
                             const double* c, double* part, double* out) {
     double* const py = part + (size_t)kObsZ * (S + 2);
     double* const px = py + kObsY;
+    // each pass reads the state, the z-pass the V-table too
+    const double state = (double)S * sizeof(cx<T>) * (double)d.npts;
+    const double vtab = S * (S + 1) / 2 * sizeof(double) * (double)d.npts;
     {
       auto k = k3d_obs_z<T, SC, S, CZ>;
       const size_t lds = (size_t)CZ * N * sizeof(cx<T>);
       const hipError_t e = set_lds(k, lds);
       if (e != hipSuccess) return e;
+      TimedLaunch tl(d, KIND_ZPASS, state + vtab);
       hipLaunchKernelGGL(k, dim3(N / CZ, N), dim3(CZ * SC::TPC), lds, d.stream, psi, vraw,
                          (const cx<T>*)d.tw[0], c[0], part);
     }
@@ -892,6 +896,7 @@ struct Passes {
       const size_t lds = y_lds_elems<T, N>(C) * sizeof(cx<T>);
       const hipError_t e = set_lds(k, lds);
       if (e != hipSuccess) return e;
+      TimedLaunch tl(d, KIND_YPASS, state);
       hipLaunchKernelGGL(k, dim3(N / C, N, S), dim3(C * XS::TPC), lds, d.stream, psi,
                          (const cx<T>*)d.tw[1], c[1], py);
     }
@@ -900,9 +905,12 @@ struct Passes {
       const size_t lds = x_lds_elems<T, N>(ROWS) * sizeof(cx<T>);
       const hipError_t e = set_lds(k, lds);
       if (e != hipSuccess) return e;
+      TimedLaunch tl(d, KIND_XPASS, state);
       hipLaunchKernelGGL(k, dim3(N / ROWS, N, S), dim3(ROWS * XS::TPC), lds, d.stream, psi,
                          (const cx<T>*)d.tw[2], c[2], px);
     }
+    TimedLaunch tl(d, KIND_OTHER,
+                   ((double)kObsZ * (S + 2) + kObsY + kObsX) * sizeof(double));
     hipLaunchKernelGGL((k3d_obs_final<S>), dim3(S + 2), dim3(kObsFinal), 0, d.stream, part,
                        kObsZ, kObsY + kObsX, out);
     return hipGetLastError();
@@ -1143,6 +1151,7 @@ size_t k3d_obs_partials(int n, int S, bool f64) {
 
 hipError_t k3d_observe(const DevView& d, const void* psi, const double* vraw, const double* c,
                        double* part, double* out) {
+  if (d.timer) d.timer->break_chain();  // untimed work may precede this call
   return dispatch(d.n[0], d.S, d.f64, [&]<typename T, class SC, int S>() {
     return Passes<T, SC, S>::observe(d, (const cx<T>*)psi, vraw, c, part, out);
   });

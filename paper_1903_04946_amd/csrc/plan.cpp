@@ -1084,6 +1084,7 @@ sop_status trap3d_run(sop_plan* p, void* psi, int count, int64_t nsteps, double 
 // written before it is read).  Synchronises the plan's stream.
 sop_status trap_run(sop_plan* p, void* psi, int count, int64_t nsteps, double tol, int max_iter,
                     char* base, const TrapLayout& lay, bool allow_graphs, int64_t* iterations) {
+  if (p->timer) p->timer->break_chain();  // untimed work may precede this call
   if (lay.three_d)
     return trap3d_run(p, psi, count, nsteps, tol, max_iter, base, lay, allow_graphs, iterations);
   const int nst = lay.nst;
@@ -1244,6 +1245,7 @@ sop_status sop_interpolate(const sop_plan* src, const void* psi_src, sop_plan* d
   double2* const T1 = (double2*)(wbase + wel);  // wel is a multiple of 128
   double2* const T2 = T1 + t1;
   const DevView& d = dst->dv;
+  if (d.timer) d.timer->break_chain();  // untimed work may precede this call
   if (!reuse && !empty) {
     dst->iws_valid = false;
     sop::TimedLaunch tl(d, sop::KIND_OTHER, (double)wel * sizeof(double));
@@ -1463,6 +1465,7 @@ sop_status sop_propagate_driven(sop_plan* p, void* psi, int64_t nsteps, const do
   HIPTRY(hipMemcpyAsync(p->d_drive, drive, ns * sizeof(double), hipMemcpyHostToDevice, st));
   // one action at a time, each potential action with its own V = V0 + s D
   sop::DevView d = p->dv;
+  if (d.timer) d.timer->break_chain();  // untimed work may precede this call
   d.graphs = nullptr;
   d.nact = 1;
   d.mid = -1;
