@@ -22,6 +22,8 @@
 // carries the 1/n_d of the unnormalised inverse transform.
 #pragma once
 
+#include <type_traits>
+
 #include "eigen.hpp"
 #include "fft_core.hpp"
 #include "internal.hpp"
@@ -562,6 +564,43 @@ constexpr bool plane_fits() {
   return plane_lds_elems<T, SC>() * sizeof(cx<T>) <= 160 * 1024 && SC::N * SC::TPC <= 1024;
 }
 
+// Workgroups of up to 512 threads take the columns by waves, with the twiddles
+// in registers.  Of 1024 threads (128^3 FP32) each has 128 registers, which do
+// not hold them (34 spilled), and a wave's 8 columns would be 64-byte pieces: 64
+// neighbouring columns a wave there, block barriers between the columns' stages
+// and twiddles read from LDS (S = 3, five TJ-4 steps: 1425 -> 1325 us).
+template <class SC>
+constexpr bool plane_waves() {
+  return SC::N * SC::TPC <= 512;
+}
+// One pencil's transforms with the twiddles in registers (REGS) or in LDS.
+template <typename T, class SC, bool REGS>
+struct PlaneTw {
+  TwRegs<T, SC> r;
+  __device__ __forceinline__ void load(const cx<T>* tw, int t) { r.load(tw, t); }
+  template <class Sync, class Lay>
+  __device__ __forceinline__ void forward(cx<T> (*v)[SC::E], cx<T>* lds, const Lay& lay, int t) {
+    fft_forward<SC, Sync>(v, lds, lay, r, t);
+  }
+  template <class Sync, class Lay>
+  __device__ __forceinline__ void inverse(cx<T> (*v)[SC::E], cx<T>* lds, const Lay& lay, int t) {
+    fft_inverse<SC, Sync>(v, lds, lay, r, t);
+  }
+};
+template <typename T, class SC>
+struct PlaneTw<T, SC, false> {
+  const cx<T>* tw;
+  __device__ __forceinline__ void load(const cx<T>* src, int) { tw = src; }
+  template <class Sync, class Lay>
+  __device__ __forceinline__ void forward(cx<T> (*v)[SC::E], cx<T>* lds, const Lay& lay, int t) {
+    fft_forward<SC, 1, Sync>(v, lds, lay, tw, t);
+  }
+  template <class Sync, class Lay>
+  __device__ __forceinline__ void inverse(cx<T> (*v)[SC::E], cx<T>* lds, const Lay& lay, int t) {
+    fft_inverse<SC, 1, Sync>(v, lds, lay, tw, t);
+  }
+};
+
 // `kin` = the three per-axis factors [f_z | f_y | f_x] of one kinetic set.
 template <typename T, class SC>
 __device__ __forceinline__ void plane_body(cx<T>* __restrict__ psi_s,
@@ -570,10 +609,13 @@ __device__ __forceinline__ void plane_body(cx<T>* __restrict__ psi_s,
                                            int z) {
   constexpr int N = SC::N, E = SC::E, TPC = SC::TPC;
   constexpr int P = N + N / 16;  // padded row stride in LDS
+  constexpr bool WAVES = plane_waves<SC>();
+  using ColSync = std::conditional_t<WAVES, WaveSync, BlockSync>;
   const int lane = threadIdx.x;
-  // column layout: a wave holds 64 / TPC whole columns
+  // column layout: with WAVES a wave holds 64 / TPC whole columns
   constexpr int CW = 64 / TPC;
-  const int col = lane / 64 * CW + lane % CW, tc = lane % 64 / CW;
+  const int col = WAVES ? lane / 64 * CW + lane % CW : lane % N;
+  const int tc = WAVES ? lane % 64 / CW : lane / N;
   const int tr = lane % TPC, row = lane / TPC;  // row layout
   constexpr int64_t plane = (int64_t)N * N;
   const auto base = rsrc(psi_s + z * plane, (uint32_t)plane);
@@ -594,14 +636,15 @@ __device__ __forceinline__ void plane_body(cx<T>* __restrict__ psi_s,
   const LayStrided lcol{col, 0, N};
   const LayPadded lrow{row * P, 0};
   const T csign = conj ? (T)-1 : (T)1;
-  __syncthreads();
-  // y round trip (columns)
-  TwRegs<T, SC> tws;
+  // y round trip (columns); without WAVES the first exchange's barrier orders
+  // the staged tables
+  if constexpr (WAVES) __syncthreads();
+  PlaneTw<T, SC, WAVES> tws;
   tws.load(twy, tc);
-  fft_forward<SC, WaveSync>(v, lds, lcol, tws, tc);
+  tws.template forward<ColSync>(v, lds, lcol, tc);
   axis_phase<T, SC, 1>(v, twy + 2 * AS, csign, tc);
-  fft_inverse<SC, WaveSync>(v, lds, lcol, tws, tc);
-  __syncthreads();
+  tws.template inverse<ColSync>(v, lds, lcol, tc);
+  if constexpr (WAVES) __syncthreads();
   // columns -> rows
 #pragma unroll
   for (int q = 0; q < E; ++q) lds[own_idx<N, E, SC::RF>(tc, q) * P + col] = v[0][q];
@@ -610,10 +653,10 @@ __device__ __forceinline__ void plane_body(cx<T>* __restrict__ psi_s,
 #pragma unroll
   for (int q = 0; q < E; ++q) v[0][q] = lds[row * P + own_idx<N, E, SC::RF>(tr, q)];
   WaveSync::sync();
-  // x round trip (rows)
-  fft_forward<SC, WaveSync>(v, lds, lrow, tws, tr);
+  // x round trip (rows, whole ones in a wave)
+  tws.template forward<WaveSync>(v, lds, lrow, tr);
   axis_phase<T, SC, 1>(v, twy + 3 * AS, csign, tr);
-  fft_inverse<SC, WaveSync>(v, lds, lrow, tws, tr);
+  tws.template inverse<WaveSync>(v, lds, lrow, tr);
 #pragma unroll
   for (int q = 0; q < E; ++q) st(base, row * N + own_idx<N, E, SC::RF>(tr, q), v[0][q]);
 }

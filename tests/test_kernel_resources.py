@@ -1,0 +1,55 @@
+"""Registers of the built kernels (no GPU needed): kernels whose spills to
+scratch memory were measured as lost time keep to what they were measured at."""
+import os
+import struct
+
+import pytest
+
+from paper_1903_04946_amd import soprop
+
+
+def sections(elf):
+    off, = struct.unpack_from("<Q", elf, 40)
+    size, count, names = struct.unpack_from("<HHH", elf, 58)
+    heads = [struct.unpack_from("<IIQQQQIIQQ", elf, off + i * size) for i in range(count)]
+    base = heads[names][4]
+    for h in heads:
+        name = elf[base + h[0]:elf.index(b"\0", base + h[0])].decode()
+        yield name, h[1], elf[h[4]:h[4] + h[5]]
+
+
+@pytest.fixture(scope="module")
+def kernels():
+    """{mangled name: metadata} of every code object in the library."""
+    msgpack = pytest.importorskip("msgpack")
+    if not os.path.exists(soprop.LIB_PATH):
+        import paper_1903_04946_amd.build as b
+        b.build()
+    out = {}
+    with open(soprop.LIB_PATH, "rb") as f:
+        library = f.read()
+    bundle = next(data for name, _, data in sections(library) if name == ".hip_fatbin")
+    at = bundle.find(b"\x7fELF")
+    while at >= 0:
+        for _, kind, data in sections(bundle[at:]):
+            if kind != 7:  # SHT_NOTE
+                continue
+            owner, size, note = struct.unpack_from("<III", data)
+            if note != 32:  # NT_AMDGPU_METADATA
+                continue
+            start = 12 + (owner + 3) // 4 * 4
+            meta = msgpack.unpackb(data[start:start + size], strict_map_key=False)
+            out.update((k[".name"], k) for k in meta["amdhsa.kernels"])
+        at = bundle.find(b"\x7fELF", at + 4)
+    assert out
+    return out
+
+
+def spills(kernels, *parts):
+    found = {n: k[".vgpr_spill_count"] for n, k in kernels.items() if all(p in n for p in parts)}
+    assert found, parts
+    return found
+
+
+def test_plane_pass_does_not_spill(kernels):
+    assert not any(spills(kernels, "k3d_plane").values())
