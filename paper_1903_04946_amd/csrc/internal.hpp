@@ -174,6 +174,13 @@ struct TimedLaunch {
   }
 };
 
+// Whether VTV runs on 1D grids merge their step boundaries.  For two FP64
+// surfaces of 8192 points (1024 threads, 128 registers each) the walk over a
+// merged run costs 6-12% and a merged boundary saves one potential action a
+// step, 1 of 55 with triple-jump-8: 500 substeps 23.3 ms merged, 22.3 ms not.
+// (A TVT boundary saves a kinetic action, and is merged.)
+constexpr bool merge_potential(int n, int S, bool f64) { return !(n == 8192 && S == 2 && f64); }
+
 // Two surfaces of n = 256 W points run on W waves of 64 lanes (W = 1, 2, 4, 8;
 // body_1d_waves.hpp); 0: the general body serves the length.
 __host__ __device__ constexpr int wave_body(int n, int S) {

@@ -10,7 +10,7 @@ namespace {
 using namespace s1d;
 
 // PL = pencils exchanged through LDS at once (S, or 1 when S pencils do not fit).
-template <typename T, class SC, int S, int PL>
+template <typename T, class SC, int S, int PL, bool MERGE = true>
 __global__ void __launch_bounds__(SC::TPC)
     k1d_prop_kernel(cx<T>* __restrict__ psi, const cx<T>* __restrict__ vexp,
                     const cx<T>* __restrict__ kin, const cx<T>* __restrict__ tw,
@@ -18,7 +18,8 @@ __global__ void __launch_bounds__(SC::TPC)
   extern __shared__ char smem_raw[];
   cx<T>* lds = reinterpret_cast<cx<T>*>(smem_raw);
   psi += (size_t)blockIdx.x * S * SC::N;  // one workgroup per state
-  run_1d<T, SC, S, PL>(psi, vexp, kin, tw, prog, nact, nsteps, conj, mid, lds);
+  run_1d<T, SC, S, PL, guard_default<T>(SC::N), MERGE>(psi, vexp, kin, tw, prog, nact, nsteps,
+                                                       conj, mid, lds);
 }
 
 // Two surfaces of 256 W points: the body on W waves.
@@ -118,12 +119,16 @@ hipError_t launch_prop(const DevView& d, void* psi, int64_t nsteps, int conj, in
                        (const cx<T>*)d.vexp, (const cx<T>*)d.kin, (const cx<T>*)d.tw[0], d.prog_1d(),
                        d.nact, nsteps, conj, d.merged());
   } else {
-    auto k = k1d_prop_kernel<T, SC, S, 1>;
+    // runs without merged boundaries have a kernel of their own where the
+    // other one's walk costs registers
+    constexpr bool PLAIN = !merge_potential(SC::N, S, std::is_same<T, double>::value);
+    auto k = PLAIN && d.mid < 0 ? k1d_prop_kernel<T, SC, S, 1, !PLAIN>
+                                : k1d_prop_kernel<T, SC, S, 1>;
     const hipError_t e = set_lds((const void*)k, one);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k, dim3(count), dim3(SC::TPC), one, d.stream, (cx<T>*)psi,
-                       (const cx<T>*)d.vexp, (const cx<T>*)d.kin, (const cx<T>*)d.tw[0], d.prog_1d(),
-                       d.nact, nsteps, conj, d.merged());
+                       (const cx<T>*)d.vexp, (const cx<T>*)d.kin, (const cx<T>*)d.tw[0],
+                       d.prog_1d(), d.nact, nsteps, conj, d.merged());
   }
   return hipGetLastError();
 }

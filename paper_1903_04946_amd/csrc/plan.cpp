@@ -616,7 +616,7 @@ sop_status sop_plan_create_with_allocator(const sop_plan_desc* desc, void* hip_s
   const ld cmid = (ld)q.a.front() + (ld)q.a.back();
   const bool both = nA > nB && nB > 0;  // the program begins and ends with an A action
   p->tmid = both && !q.a_is_v;
-  p->vmid = both && q.a_is_v && p->ndim == 1;
+  p->vmid = both && q.a_is_v && p->ndim == 1 && sop::merge_potential(p->n[0], S, f64);
   std::vector<double> ktaus = p->ttaus;
   if (p->tmid) ktaus.push_back((double)(cmid * (ld)p->dt));
   std::vector<double> dtaus = p->vtaus;

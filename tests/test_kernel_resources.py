@@ -53,3 +53,11 @@ def spills(kernels, *parts):
 
 def test_plane_pass_does_not_spill(kernels):
     assert not any(spills(kernels, "k3d_plane").values())
+
+
+def test_two_fp64_surfaces_of_8192_points(kernels):
+    """Plain runs and batch members (a kernel for runs with merged boundaries
+    may spill more): 57 registers a lane when a substep took 14.6 us."""
+    single = spills(kernels, "k1d_prop_kernelIdNS_5SchedILi8192E", "Li2ELi1E")
+    assert min(single.values()) <= 57
+    assert max(spills(kernels, "k1b_kernelIdNS_5SchedILi8192ELi8E", "Li2ELi1E").values()) <= 57
