@@ -191,7 +191,8 @@ __host__ __device__ constexpr int wave_body(int n, int S) {
 // of a wave is a run of 32 entries a surface instead of 16-byte pieces 16 W
 // bytes apart.  Place of point x, and of frequency k:
 __host__ __device__ inline int wave_order_x(int W, int x) {
-  const int w = x % W, h = (x / W) % 4, g = (x / (4 * W)) % 8, r = x / (32 * W);
+  const int b = (W > 1) + (W > 2) + (W > 4);  // log2 W (W may be known at run time only)
+  const int w = x & (W - 1), h = (x >> b) & 3, g = (x >> (b + 2)) & 7, r = x >> (b + 5);
   return (8 * w + r) * 32 + 8 * h + g;
 }
 __host__ __device__ inline int wave_order_k(int W, int k) {

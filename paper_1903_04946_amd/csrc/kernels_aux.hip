@@ -25,8 +25,8 @@ namespace sop {
 namespace {
 
 // Destination index of (table u, entry e, point x): structure of arrays for
-// 1D (tile = 0, or -W with the points in wave order) or the z-pass tile layout for a cubic 3D grid of side n
-// (x below 2^31: 32-bit divisions).
+// 1D (tile = 0, or -W with the points in wave order) or the z-pass tile layout
+// for a cubic 3D grid of side n (x below 2^31: 32-bit divisions).
 __device__ __forceinline__ int64_t table_index(int64_t npts, int NE, int tile, int n, int u, int e,
                                                int64_t x) {
   if (tile <= 0)
