@@ -43,8 +43,8 @@ using T2048 = Sched<2048, 4, RList<4, 4, 4, 4, 4, 2>, RList<2, 4, 4, 4, 4, 4>, 4
 using T4096 = Sched<4096, 4, RList<4, 4, 4, 4, 4, 4>, RList<4, 4, 4, 4, 4, 4>, 4, 4>;
 using T8192 = S8192;  // 1024 threads already
 // At 1024 threads a wave gets at most 128 VGPRs, so the 4096- and 8192-point
-// kernels spill (gfx950 build: 160 / 504 bytes per lane at 4096 points with
-// one / two surfaces, 212 / 1592 at 8192); 512 threads of eight values per
+// kernels spill (gfx950 build: 164 / 488 bytes per lane at 4096 points with
+// one / two surfaces, 200 / 1616 at 8192); 512 threads of eight values per
 // thread spill as much at 4096 points and two surfaces (460 bytes).
 
 typedef cx<double> cd_t;
@@ -52,6 +52,12 @@ typedef cx<double> cd_t;
 __device__ __forceinline__ cd_t cdiv(cd_t a, cd_t b) {
   const double den = b.re * b.re + b.im * b.im;
   return {(a.re * b.re + a.im * b.im) / den, (a.im * b.re - a.re * b.im) / den};
+}
+
+// c - a b in four fused operations.
+__device__ __forceinline__ cd_t sub_prod(cd_t c, cd_t a, cd_t b) {
+  return {fused(a.im, b.im, fused(-a.re, b.re, c.re)),
+          fused(-a.im, b.re, fused(-a.re, b.im, c.im))};
 }
 
 // Workgroup sums of K doubles (TPC a multiple of 64); every thread receives
@@ -193,7 +199,14 @@ __global__ void __launch_bounds__(SC::TPC) __attribute__((amdgpu_waves_per_eu(2)
           for (int q = 0; q < E; ++q) {
             const int idx = s * N + own_idx<N, E, SC::RF>(t, q);
             psi[idx] = cadd(psi[idx], cmul(alpha, p[s][q]));
-            const cd_t rn = csub(rbuf[idx], cmul(alpha, v[s][q]));
+            // with eight values a thread (8192 points) the product's own
+            // registers are 64 spilled ones more (one surface, a solve to
+            // 1e-9: 33.6 against 26.9 ms); 4096 points x 2 lose 2% without
+            cd_t rn;
+            if constexpr (E >= 8)
+              rn = sub_prod(rbuf[idx], alpha, v[s][q]);
+            else
+              rn = csub(rbuf[idx], cmul(alpha, v[s][q]));
             rbuf[idx] = rn;
             v[s][q] = rn;
             s3[0] += rn.re * rn.re + rn.im * rn.im;
