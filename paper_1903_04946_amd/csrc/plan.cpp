@@ -12,6 +12,7 @@
 #include <cstdio>
 #include <algorithm>
 #include <cstring>
+#include <mutex>
 #include <new>
 #include <string>
 #include <vector>
@@ -241,7 +242,7 @@ struct sop_plan {
   void* d_akin = nullptr;
   double* d_part = nullptr;
   double* d_out = nullptr;
-  double* h_out = nullptr;  // pinned: the sums of an observables call (from the first one on)
+  double* h_out = nullptr;  // PinnedSlots slot of an observables call's sums (from the first one on)
   size_t table_bytes = 0;
   bool eig_form = false;  // d_vexp holds the compact eigen form (3D FP64, S >= 2)
   double vbound = 0;      // max over points of max_i sum_j |V_ij| (bounds |lam|)
@@ -301,6 +302,50 @@ hipError_t dalloc(sop_plan* p, T** ptr, size_t bytes) {
   return e;
 }
 
+// Pinned host memory for the sums of observables calls: one page for the
+// process, a 64-byte slot a plan, taken at the plan's first call and returned
+// with the plan.  (A pinned buffer of each plan's own cost 25-35 us at that
+// call and as much when the plan goes; a call takes 19 us at 256 points.)  With
+// no slot free the sums are copied from device memory.
+class PinnedSlots {
+ public:
+  static double* acquire() {
+    std::lock_guard<std::mutex> lock(mutex());
+    State& s = state();
+    if (!s.base && hipHostMalloc((void**)&s.base, kSlots * kDoubles * sizeof(double),
+                                 hipHostMallocPortable) != hipSuccess) {
+      s.base = nullptr;
+      (void)hipGetLastError();
+    }
+    for (int i = 0; s.base && i < kSlots; ++i)
+      if (!s.used[i]) {
+        s.used[i] = true;
+        return s.base + (size_t)i * kDoubles;
+      }
+    return nullptr;
+  }
+  static void release(double* slot) {
+    std::lock_guard<std::mutex> lock(mutex());
+    State& s = state();
+    s.used[(slot - s.base) / kDoubles] = false;
+  }
+
+ private:
+  static constexpr int kSlots = 64, kDoubles = 8;
+  struct State {
+    double* base = nullptr;
+    bool used[kSlots] = {};
+  };
+  static std::mutex& mutex() {
+    static std::mutex* m = new std::mutex;  // outlives plans destroyed at exit
+    return *m;
+  }
+  static State& state() {
+    static State* s = new State;
+    return *s;
+  }
+};
+
 void free_plan(sop_plan* p) {
   if (!p) return;
   void* bufs[] = {p->d_base, p->d_atab, p->d_akin,  p->d_vbase, p->d_dv,  p->d_theta,
@@ -314,7 +359,7 @@ void free_plan(sop_plan* p) {
     else
       (void)hipFree(b);
   }
-  if (p->h_out) (void)hipHostFree(p->h_out);
+  if (p->h_out) PinnedSlots::release(p->h_out);
   delete p->timer;
   delete p;
 }
@@ -844,18 +889,21 @@ sop_status sop_observables(sop_plan* p, const void* psi, double* out) {
     c[a] = 0.5 * p->inv_mass[a] * kap * kap / p->n[a];
   }
   // the last kernel writes the sums to pinned host memory (no copy to wait for)
-  if (!p->h_out && hipHostMalloc((void**)&p->h_out, 8 * sizeof(double), hipHostMallocDefault) !=
-                       hipSuccess) {
-    p->h_out = nullptr;
-    (void)hipGetLastError();
-    return fail(SOP_ERR_NOMEM, "pinned memory for the observables");
-  }
+  if (!p->h_out) p->h_out = PinnedSlots::acquire();
+  double* const sums = p->h_out ? p->h_out : p->d_out;
   if (p->ndim == 1)
-    HIPTRY(sop::k1d_observe(p->dv, psi, p->d_vraw, c[0], p->h_out));
+    HIPTRY(sop::k1d_observe(p->dv, psi, p->d_vraw, c[0], sums));
   else
-    HIPTRY(sop::k3d_observe(p->dv, psi, p->d_vraw, c, p->d_part, p->h_out));
+    HIPTRY(sop::k3d_observe(p->dv, psi, p->d_vraw, c, p->d_part, sums));
+  double raw[8];
+  if (!p->h_out)
+    HIPTRY(hipMemcpyAsync(raw, p->d_out, (p->S + 2) * sizeof(double), hipMemcpyDeviceToHost,
+                          p->dv.stream));
   HIPTRY(hipStreamSynchronize(p->dv.stream));
-  const volatile double* const raw = p->h_out;
+  if (p->h_out) {
+    const volatile double* const h = p->h_out;
+    for (int k = 0; k < p->S + 2; ++k) raw[k] = h[k];
+  }
   const int S = p->S;
   double norm = 0;
   for (int s = 0; s < S; ++s) norm += raw[s] * p->dV;
