@@ -381,9 +381,8 @@ hipError_t adjoint_seed(const DevView& d, void* lam, const void* psi, const doub
 // qacc in the accumulator's tile layout with `cols` columns per tile
 hipError_t grad_reduce(const DevView& d, const double* qacc, int cols, const double* dv,
                        const EntryMasks& mask, int nparams, double* partials, double* out_dev);
-// out_dev[0..S) = sum |psi_s|^2, out_dev[S] = sum psi^dag V psi (raw sums)
-hipError_t pops_reduce(const DevView& d, const void* psi, const double* vraw_dev,
-                       double* partials, double* out_dev);
+// out_dev[0..S) = sum |psi_s|^2 of an FP64 state
+hipError_t pops_reduce(const DevView& d, const void* psi, double* partials, double* out_dev);
 // ------------------------------------------------------------------ batches
 // Device descriptor of one 1D member of a batch (kernels_batch1d.hip).
 struct BMember1 {

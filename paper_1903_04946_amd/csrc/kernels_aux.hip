@@ -11,7 +11,7 @@
 // triangle is stored structure-of-arrays, [unique][entry][point] for 1D
 // grids, or tile-contiguous for the 3D z-pass ([unique][tile][z][entry][col]).
 //
-// Reductions: surface populations and <V> from psi, <psi|phi> and distances
+// Reductions: surface populations of an FP64 state, <psi|phi> and distances
 // (the observables' sums with <T> are in kernels_1d.hip and kernels_3d.hip,
 // with the transforms they need); every sum is FP64 with a fixed block
 // count and a fixed-order tree, so results are bitwise reproducible.
@@ -114,39 +114,23 @@ __device__ void block_sum(double (&acc)[NV], double* out) {
   }
 }
 
-// Per block: sum_x |psi_s(x)|^2 for each s, and sum_x Re(psi(x)^dag V(x) psi(x)).
-template <typename T, int S>
+// Per block: sum_x |psi_s(x)|^2 for each s.
+template <int S>
 __global__ void __launch_bounds__(kReduceThreads)
-    k_obs_points(const cx<T>* __restrict__ psi, const double* __restrict__ vraw, int64_t npts,
-                 double* __restrict__ partials) {
-  double acc[S + 1];
+    k_populations(const cx<double>* __restrict__ psi, int64_t npts,
+                  double* __restrict__ partials) {
+  double acc[S];
 #pragma unroll
-  for (int v = 0; v <= S; ++v) acc[v] = 0.0;
+  for (int s = 0; s < S; ++s) acc[s] = 0.0;
   for (int64_t x = (int64_t)blockIdx.x * kReduceThreads + threadIdx.x; x < npts;
        x += (int64_t)gridDim.x * kReduceThreads) {
-    double re[S], im[S];
 #pragma unroll
     for (int s = 0; s < S; ++s) {
-      const cx<T> p = psi[s * npts + x];
-      re[s] = (double)p.re;
-      im[s] = (double)p.im;
-      acc[s] += re[s] * re[s] + im[s] * im[s];
+      const cx<double> p = psi[s * npts + x];
+      acc[s] += p.re * p.re + p.im * p.im;
     }
-    int e = 0;
-    double ev = 0.0;
-#pragma unroll
-    for (int i = 0; i < S; ++i)
-#pragma unroll
-      for (int j = i; j < S; ++j) {
-        const double vij = vraw[(int64_t)e * npts + x];
-        // Re(conj(psi_i) psi_j), counted twice off the diagonal
-        const double rr = re[i] * re[j] + im[i] * im[j];
-        ev += (i == j ? 1.0 : 2.0) * vij * rr;
-        ++e;
-      }
-    acc[S] += ev;
   }
-  block_sum<S + 1>(acc, partials + (size_t)blockIdx.x * (S + 1));
+  block_sum<S>(acc, partials + (size_t)blockIdx.x * S);
 }
 
 template <typename T>
@@ -345,14 +329,6 @@ hipError_t form_impl(const DevView& d, const double* vraw, const double* taus, i
   return hipGetLastError();
 }
 
-template <int S, typename T>
-hipError_t obs_points_impl(const DevView& d, const void* psi, const double* vraw,
-                           double* partials) {
-  hipLaunchKernelGGL((k_obs_points<T, S>), dim3(kReduceBlocks), dim3(kReduceThreads), 0,
-                     d.stream, (const cx<T>*)psi, vraw, d.npts, partials);
-  return hipGetLastError();
-}
-
 }  // namespace
 
 hipError_t form_vexp(const DevView& d, const double* vraw_dev, const double* taus, int ntau,
@@ -447,21 +423,15 @@ hipError_t grad_reduce(const DevView& d, const double* qacc, int cols, const dou
   return hipGetLastError();
 }
 
-hipError_t pops_reduce(const DevView& d, const void* psi, const double* vraw_dev,
-                       double* partials, double* out_dev) {
-  hipError_t e;
-  switch (d.S) {
-    case 1: e = d.f64 ? obs_points_impl<1, double>(d, psi, vraw_dev, partials)
-                      : obs_points_impl<1, float>(d, psi, vraw_dev, partials); break;
-    case 2: e = d.f64 ? obs_points_impl<2, double>(d, psi, vraw_dev, partials)
-                      : obs_points_impl<2, float>(d, psi, vraw_dev, partials); break;
-    case 3: e = d.f64 ? obs_points_impl<3, double>(d, psi, vraw_dev, partials)
-                      : obs_points_impl<3, float>(d, psi, vraw_dev, partials); break;
-    default: return hipErrorInvalidValue;
-  }
+hipError_t pops_reduce(const DevView& d, const void* psi, double* partials, double* out_dev) {
+  auto k = d.S == 1 ? k_populations<1> : d.S == 2 ? k_populations<2> : k_populations<3>;
+  if (!d.f64 || d.S < 1 || d.S > 3) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k, dim3(kReduceBlocks), dim3(kReduceThreads), 0, d.stream,
+                     (const cx<double>*)psi, d.npts, partials);
+  const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_final, dim3(1), dim3(kReduceThreads), 0, d.stream, partials, kReduceBlocks,
-                     d.S + 1, out_dev);
+                     d.S, out_dev);
   return hipGetLastError();
 }
 

@@ -1653,9 +1653,9 @@ sop_status sop_adjoint_forward(sop_plan* p, const void* psi0, int64_t nsteps, in
     HIPTRY(sop::k3d_propagate(p->dv, w + lay.psi, k, 0));
     done += k;
   }
-  HIPTRY(sop::pops_reduce(p->dv, w + lay.psi, p->d_vraw, p->d_part, p->d_out));
+  HIPTRY(sop::pops_reduce(p->dv, w + lay.psi, p->d_part, p->d_out));
   double raw[8];
-  HIPTRY(hipMemcpyAsync(raw, p->d_out, (p->S + 1) * sizeof(double), hipMemcpyDeviceToHost, s));
+  HIPTRY(hipMemcpyAsync(raw, p->d_out, p->S * sizeof(double), hipMemcpyDeviceToHost, s));
   HIPTRY(hipStreamSynchronize(s));
   for (int q = 0; q < p->S; ++q) pops_out[q] = raw[q] * p->dV;
   return SOP_OK;
