@@ -197,7 +197,8 @@ sop_status sop_plan_create(const sop_plan_desc* desc, void* hip_stream, sop_plan
  * scratch space -- comes from alloc and goes back through free when the
  * plan is destroyed (after sop_plan_destroy has synchronised the plan's
  * stream), so that a framework's caching allocator (PyTorch's) owns the
- * memory.  Batches and HIP graph objects keep their own small allocations. */
+ * memory.  Batches and HIP graph objects keep their own small allocations, and
+ * the process keeps one page of pinned host memory for observables' sums. */
 typedef struct {
   void* ctx;
   void* (*alloc)(void* ctx, size_t bytes, void* stream);

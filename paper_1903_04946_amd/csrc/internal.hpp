@@ -125,7 +125,8 @@ struct DevView {
   std::vector<int> hprog;      // host copy of the step program
   // action of a step boundary inside one call: the last action of a step and
   // the first of the next, where both are kinetic (TVT) or, on 1D grids, both
-  // potential (VTV), as one action with the summed coefficient; -1: none
+  // potential (VTV, merge_potential), as one action with the summed
+  // coefficient; -1: none
   int mid = -1;
   // 3D eigen form: a driven action forms its V in the z-pass (v0 set)
   DrivenV driven;

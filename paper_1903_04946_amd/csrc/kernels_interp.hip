@@ -333,8 +333,8 @@ hipError_t interp_weights(hipStream_t s, double* Wt, int n, double lo, double hi
 
 hipError_t interp_axis(hipStream_t s, const InterpAxis& g, bool krow) {
   if (g.M < 1 || g.N < 1 || g.K < 1 || g.batch < 1) return hipErrorInvalidValue;
-  // the row tile that pads M least (the larger one on a tie: fewer reads of
-  // the columns)
+  // 128 rows where they pad M no more than smaller tiles do (fewer reads of the
+  // columns), 32 for up to 32 points, else 64
   const int p32 = (g.M + 31) / 32, p64 = (g.M + 63) / 64 * 2, p128 = (g.M + 127) / 128 * 4;
   if (p128 <= p64 && p128 <= p32) return launch_axis<128, 4, 4>(s, g, krow);
   if (p64 <= p32 || g.M > 32) return launch_axis<64, 2, 4>(s, g, krow);

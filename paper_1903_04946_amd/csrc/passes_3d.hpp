@@ -133,31 +133,7 @@ __device__ __forceinline__ void axis_phase(cx<T> (*v)[SC::E], const cx<T>* __res
   }
 }
 
-// ---------------------------------------------------------------- z-pass
-// Potential tables are stored per tile of TC x-columns: for table u, tile
-// (y, x / TC) holds [z][entry][x % TC] contiguously, N * NE * TC complex, so
-// a tile reads its table as one contiguous stream.  The pass tile is C
-// columns wide (C divides TC); block (bx, by) owns columns bx*C .. bx*C+C-1
-// of row y = by.  `psi` is one state [S][N^3]; `fz` the z factor of the
-// kinetic set (AX_KIN only).
-//
-// Table entries are cx<T>, in FP32 the pairs (rounded, residue) of
-// Split<float> (each entry's index doubled).  `lane` (here and in the y- and
-// x-pass bodies) is the thread's index in the tile, threadIdx.x unless a
-// persistent caller passes it through opaque() so that the compiler does not
-// keep every lane-derived offset live across its work loop.  `src` (here and
-// there): where the pass reads the state, psi itself when NULL (in place);
-// the pass always writes psi.
-//
-// EQ (S = 2, 3): `vexp` is instead the one compact eigen-form table, FP64 in
-// both precisions (eig_slots(S) complex double slots per point, same tile
-// layout), and `taus` the tau of each coefficient; a potential action is
-// psi <- R exp(-i tau lam) R^T psi in registers, and the two actions at a
-// step boundary share one load, one pair of rotations and one phase
-// (psi <- R exp(-i (tau_1 + tau_2) lam) R^T psi: the same operator, rounded
-// once).  The action is computed in FP64 in both precisions: an FP32 state
-// is widened, rotated and phased in FP64 and rounded once, so the FP32 form
-// carries no rounded potential operator.
+// ---------------------------------------------------------------- eigen form
 // cache-policy bits of a buffer load: non-temporal
 constexpr int kCpolNT = 2;
 
@@ -270,14 +246,40 @@ struct DrivenRead {
 // On FP64 grids of 256 points a state of two or three surfaces (537, 805 MB) is
 // beyond the last-level cache (256 MB), and little of the z-pass's output is
 // left there for the y-pass: the z-pass stores and the y-pass loads it with the
-// non-temporal hint, which spares the y-pass the write-back of what it evicts
-// (256^3 x 3: y 308 -> 281 us a pass, 292 with the stores alone; z and x the
-// same.  On the z-pass's loads, and on the y- and x-passes' stores and the
-// x-pass's loads, it gains nothing).  One surface (268 MB) partly stays, and
+// non-temporal hint, which spares the y-pass the write-back of what it evicts.
+// us a pass without -> with: 256^3 x 2 y 194 -> 175, z 313, x 201 both (a TJ-6
+// step 6.60 -> 6.41 ms); x 3 y 291 -> 281, z 548 -> 546, x 303 -> 310 (10.68 ->
+// 10.65 ms).  On the z-pass's loads, and on the y- and x-passes' stores and the
+// x-pass's loads, it gains nothing.  One surface (268 MB) partly stays, and
 // loses with the hint (3.06 -> 3.14 ms a TJ-6 step).
 template <typename T, int N, int S>
 constexpr int kStateCpol = N >= 256 && S >= 2 && sizeof(T) == 8 ? kCpolNT : 0;
 
+// ---------------------------------------------------------------- z-pass
+// Potential tables are stored per tile of TC x-columns: for table u, tile
+// (y, x / TC) holds [z][entry][x % TC] contiguously, N * NE * TC complex, so
+// a tile reads its table as one contiguous stream.  The pass tile is C
+// columns wide (C divides TC); block (bx, by) owns columns bx*C .. bx*C+C-1
+// of row y = by.  `psi` is one state [S][N^3]; `fz` the z factor of the
+// kinetic set (AX_KIN only).
+//
+// Table entries are cx<T>, in FP32 the pairs (rounded, residue) of
+// Split<float> (each entry's index doubled).  `lane` (here and in the y- and
+// x-pass bodies) is the thread's index in the tile, threadIdx.x unless a
+// persistent caller passes it through opaque() so that the compiler does not
+// keep every lane-derived offset live across its work loop.  `src` (here and
+// there): where the pass reads the state, psi itself when NULL (in place);
+// the pass always writes psi.
+//
+// EQ (S = 2, 3): `vexp` is instead the one compact eigen-form table, FP64 in
+// both precisions (eig_slots(S) complex double slots per point, same tile
+// layout), and `taus` the tau of each coefficient; a potential action is
+// psi <- R exp(-i tau lam) R^T psi in registers, and the two actions at a
+// step boundary share one load, one pair of rotations and one phase
+// (psi <- R exp(-i (tau_1 + tau_2) lam) R^T psi: the same operator, rounded
+// once).  The action is computed in FP64 in both precisions: an FP32 state
+// is widened, rotated and phased in FP64 and rounded once, so the FP32 form
+// carries no rounded potential operator.
 template <typename T, class SC, int S, int C, int TC, int AX, bool EQ = false>
 __device__ __forceinline__ void zpass_body(cx<T>* __restrict__ psi,
                                            const void* __restrict__ vexp, int nv, int iv0,
@@ -553,8 +555,11 @@ __device__ __forceinline__ void xpass_body(cx<T>* __restrict__ psi_s,
 // data and staged while these arrive; twiddles are held in registers (64^3:
 // 12.5 -> 11.9 us, 48^3: 8.1 -> 7.7 us against reads between the stages); 48
 // points take two stages, 12 x 4, not 4 x 4 x 3.  us a pass (FP64), before ->
-// now: 32^3 x 3: 4.8 -> 4.5, 48^3 x 2: 10.4 -> 7.7, 64^3 x 3: 12.6 -> 11.9
-// (of which a copy of the same data takes 2.7, 4.6 and 7.4).
+// now: 32^3 x 3: 4.8 -> 4.5, 48^3 x 2: 10.4 -> 7.7, 64^3 x 3: 12.7 -> 11.7 (of
+// which a copy of the same data takes 2.7, 4.6 and 7.4), all behind the z tile.
+// A trace shows less behind a slower z-pass, whose writes are out by its end:
+// 64^3 x 3, z + plane: 13.2 + 10.9 with neither, 10.6 + 12.7 with the z tile, 10.6 +
+// 11.7 with both; ten TJ-4 steps 798, 782 and 736 us.
 template <typename T, class SC>
 constexpr size_t plane_lds_elems() {
   return (size_t)SC::N * (SC::N + SC::N / 16) + 4 * axis_block<T, SC::N>();
