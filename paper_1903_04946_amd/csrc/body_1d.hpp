@@ -101,9 +101,9 @@ struct Walk {
 };
 
 // Whether the program is held by the lanes (Walk, one loop over the actions) or
-// read from memory by nested loops over pieces and steps.  A workgroup of N / 8
-// threads holds a piece of N / 8 entries: on long programs the grids of up to
-// 128 points spent their time refilling it (us of 1500 substeps of
+// read from memory by nested loops over pieces and steps, in the single-plan
+// kernels.  A workgroup of N / 8 threads holds a piece of N / 8 entries: on long
+// programs the grids of up to 128 points spent their time refilling it (us of 1500 substeps of
 // triple-jump-8, held / nested: FP64 16 x 1 1480 / 1060, 64 x 2 3890 / 3650, 128 x 1
 // 3290 / 3040; FP32 128 x 1 3760 / 3050).  From 512 points on the nested loops
 // lose (FP32 512 x 1 4210 / 4850; FP64 8192 x 1, 500 substeps, 12490 / 13340), and on
@@ -182,9 +182,10 @@ __device__ __forceinline__ void action(cx<T> (&v)[S][SC::E], int code, const cx<
 // PL = pencils exchanged through LDS at once (S, or 1 when S pencils do not
 // fit).  `lds` holds PL padded pencils.  With one pencil of buffer and two
 // surfaces the two transforms run interleaved (fft_forward_pair).
-// MERGE: the run may have merged step boundaries (mid).
+// MERGE: the run may have merged step boundaries (mid).  HELD: the walk.
 template <typename T, class SC, int S, int PL,
-          bool GUARD = guard_default<T>(SC::N), bool MERGE = true>
+          bool GUARD = guard_default<T>(SC::N), bool MERGE = true,
+          bool HELD = walk_held<T>(SC::N, S)>
 __device__ __forceinline__ void run_1d(cx<T>* __restrict__ psi, const cx<T>* __restrict__ vexp,
                                        const cx<T>* __restrict__ kin,
                                        const cx<T>* __restrict__ tw,
@@ -199,7 +200,7 @@ __device__ __forceinline__ void run_1d(cx<T>* __restrict__ psi, const cx<T>* __r
 #pragma unroll
     for (int q = 0; q < E; ++q) v[s][q] = psi[s * N + own_idx<N, E, SC::RF>(t0, q)];
 
-  if constexpr (walk_held<T>(N, S)) {
+  if constexpr (HELD) {
     for (Walk<SC::TPC> w(prog, nact, nsteps, mid); w.left > 0; w.next())
       action<T, SC, S, PL, GUARD>(v, w.code(), vexp, kin, tw, csign, lds, t0);
   } else {

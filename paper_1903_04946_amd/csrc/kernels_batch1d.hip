@@ -48,6 +48,21 @@ struct Alt<8192> {
 
 constexpr size_t kMaxLds = 160 * 1024;
 
+// How a member's program is walked (walk_held).  With the pointers read from
+// the member's descriptor the kernels have other registers than the
+// single-plan ones, and other lengths gain from the one loop.  Microseconds of
+// 32 members, Suzuki-6, held / nested (one variant where there are several):
+// FP64, one surface: 16 216 / 231, 64 385 / 370, 128 694 / 560, 256 577 / 777, 512
+// 67 / 90, 1024 94 / 125, 2048 157 / 169, 4096 248 / 267, 8192 643 / 661; two: 16
+// 337 / 334, 32 657 / 720, 64 685 / 829, 128 850 / 945, 4096 535 / 400, 8192
+// 1486 / 960.  FP32, one: 64 461 / 446, 128 649 / 620, 512 77 / 69, 1024 108 / 130,
+// 2048 177 / 152, 8192 606 / 571; two: 64 840 / 810, 4096 344 / 322, 8192 780 / 807.
+template <typename T>
+constexpr bool member_walk_held(int n, int S) {
+  if (sizeof(T) == 4) return (n == 1024 && S == 1) || (n == 8192 && S == 2);
+  return S == 1 ? n == 16 || n >= 256 : n >= 32 && n <= 128;
+}
+
 template <typename T, class SC, int S, int PL, bool G>
 __global__ void __launch_bounds__(SC::TPC)
     k1b_kernel(const BMember1* __restrict__ mem) {
@@ -55,8 +70,9 @@ __global__ void __launch_bounds__(SC::TPC)
   cx<T>* lds = reinterpret_cast<cx<T>*>(smem_raw);
   const BMember1 m = mem[blockIdx.x];
   if (m.nsteps <= 0) return;
-  run_1d<T, SC, S, PL, G>((cx<T>*)m.psi, (const cx<T>*)m.vexp, (const cx<T>*)m.kin,
-                          (const cx<T>*)m.tw, m.prog, m.nact, m.nsteps, m.conj, m.mid, lds);
+  run_1d<T, SC, S, PL, G, true, member_walk_held<T>(SC::N, S)>(
+      (cx<T>*)m.psi, (const cx<T>*)m.vexp, (const cx<T>*)m.kin, (const cx<T>*)m.tw, m.prog,
+      m.nact, m.nsteps, m.conj, m.mid, lds);
 }
 
 template <typename T, int W>

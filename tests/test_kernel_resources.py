@@ -63,6 +63,12 @@ def test_two_fp64_surfaces_of_8192_points(kernels):
     assert max(spills(kernels, "k1b_kernelIdNS_5SchedILi8192ELi8E", "Li2ELi1E").values()) <= 57
 
 
+def test_batch_members_of_4096_points(kernels):
+    """Two FP64 surfaces, exchanged together: 48 registers a lane when 32
+    members took 401 us (105: 508)."""
+    assert max(spills(kernels, "k1b_kernelIdNS_5SchedILi4096ELi8E", "Li2ELi2E").values()) <= 48
+
+
 def test_trapezoid_of_8192_points(kernels):
     """One surface: 63 registers a lane when a solve took 26.9 ms (127: 33.6)."""
     assert max(spills(kernels, "k1d_trap_kernelINS_5SchedILi8192E", "Li1ELi1E").values()) <= 63
