@@ -349,7 +349,8 @@ __device__ __forceinline__ void actions(cx<T> (&v)[8], const Map<W>& m, const Tw
 // twiddles, and points dealt so that neighbouring lanes take neighbouring
 // points (w) and table entries (g) in runs of 8, where the loop's ownership
 // reads and writes the state in 16-byte pieces (2048 points FP64: 7.9 -> 4.9 us,
-// 512: 3.3 -> 1.9).
+// 512: 3.3 -> 1.9).  A kernel of its own: as a branch of run it cost 256 points
+// 0.8% of every run.
 template <typename T, int W>
 __device__ __forceinline__ void potential(cx<T>* __restrict__ psi, const cx<T>* __restrict__ vexp,
                                           int idx, int conj) {
@@ -385,10 +386,6 @@ __device__ __forceinline__ void run(cx<T>* __restrict__ psi, const cx<T>* __rest
                                     const cx<T>* __restrict__ kin, const cx<T>* __restrict__ tw,
                                     const int* __restrict__ prog, int nact, int64_t nsteps,
                                     int conj, int mid, cx<T>* lds) {
-  if (nact == 1 && nsteps == 1 && (prog[0] >> 16) == OP_V) {
-    potential<T, W>(psi, vexp, prog[0] & 0xffff, conj);
-    return;
-  }
   const Map<W> m((int)threadIdx.x);
   Tw<T, W> tws;
   tws.load(tw, m);

@@ -34,6 +34,14 @@ __global__ void __launch_bounds__(wv::Dim<W>::threads)
   wv::run<T, W>(psi, vexp, kin, tw, prog, nact, nsteps, conj, mid, lds);
 }
 
+// One potential action (table entry block idx) of two surfaces of 256 W points.
+template <typename T, int W>
+__global__ void __launch_bounds__(wv::Dim<W>::threads)
+    k1d_waves_potential(cx<T>* __restrict__ psi, const cx<T>* __restrict__ vexp, int idx,
+                        int conj) {
+  wv::potential<T, W>(psi + (size_t)blockIdx.x * 2 * wv::Dim<W>::N, vexp, idx, conj);
+}
+
 // Observables of one state in one workgroup: out[0..S) = sum |psi_s|^2,
 // out[S] = sum psi^dag V psi, out[S + 1] = ck sum k^2 |F psi|^2 (k signed; FP64
 // sums in a fixed order).
@@ -105,6 +113,11 @@ hipError_t launch_prop(const DevView& d, void* psi, int64_t nsteps, int conj, in
   if constexpr (wave_body(SC::N, S) > 0) {
     constexpr int W = wave_body(SC::N, S);
     constexpr size_t bytes = wv::lds_bytes<T, W>();
+    if (d.nact == 1 && nsteps == 1 && prog_op(d.hprog[0]) == OP_V) {
+      hipLaunchKernelGGL((k1d_waves_potential<T, W>), dim3(count), dim3(wv::Dim<W>::threads), 0,
+                         d.stream, (cx<T>*)psi, (const cx<T>*)d.vexp, prog_idx(d.hprog[0]), conj);
+      return hipGetLastError();
+    }
     auto k = k1d_waves_kernel<T, W>;
     const hipError_t e = set_lds((const void*)k, bytes);
     if (e != hipSuccess) return e;
